@@ -62,12 +62,11 @@ struct Plan {
     // plan-lifetime buffers
     void *green = nullptr, *tw = nullptr, *M = nullptr, *spec = nullptr, *L = nullptr;
     int *start = nullptr, *small = nullptr;
-    int *tile_first = nullptr;  // near field: first tile of every row of cells
     double *sums = nullptr, *qr2_partial = nullptr;
     // particle buffers
     int64_t cap = 0, last_n = -1;
     int *cell_of = nullptr, *slot = nullptr, *perm = nullptr, *scell = nullptr, *pos = nullptr;
-    int *tile_row = nullptr;    // near field: row of every tile
+    int *lists = nullptr;       // near field: work lists
     int *count = nullptr, *tile_sums = nullptr;  // radix-sort histograms and scan scratch
     void *sorted = nullptr, *staged = nullptr;   // staged: out4<T>[cap] sorted-order results
     int4 *items = nullptr;                       // dense P2M items [dense_items_cap(cap, K)]
@@ -253,13 +252,12 @@ static size_t plan_bytes(const Plan *pl) {
     b += (size_t)pl->P * pl->K * t;                      // L
     b += ((size_t)pl->K + 1 + 8) * sizeof(int);                                   // starts, small
     b += 8 * sizeof(double) + (size_t)pl->n * sizeof(double);                     // sums, plane sums
-    b += (size_t)pl->n * pl->n * sizeof(int);                                     // near-field row tiles
     return b;
 }
 
 static size_t particle_bytes(const Plan *pl, int64_t n) {
     return (size_t)n * (5 * sizeof(int) + 8 * pl->tsize) +
-           sizeof(int) * (size_t)(near_tile_capacity(n, pl->n) + bin_hist_ints(n) +
+           sizeof(int) * (size_t)(near_list_ints(n, pl->n) + bin_hist_ints(n) +
                                   bin_scan_tiles(n)) +
            sizeof(int4) * (size_t)dense_items_cap(n, pl->K) +
            sizeof(float) * (size_t)dense_slots_cap(n) * (pl->P + 1);
@@ -273,12 +271,12 @@ static void free_particles(Plan *pl) {
     hipFree(pl->sorted);
     hipFree(pl->pos);
     hipFree(pl->staged);
-    hipFree(pl->tile_row);
+    hipFree(pl->lists);
     hipFree(pl->count);
     hipFree(pl->tile_sums);
     hipFree(pl->items);
     hipFree(pl->partial);
-    pl->cell_of = pl->slot = pl->perm = pl->scell = pl->pos = pl->tile_row = nullptr;
+    pl->cell_of = pl->slot = pl->perm = pl->scell = pl->pos = pl->lists = nullptr;
     pl->count = pl->tile_sums = nullptr;
     pl->sorted = pl->staged = nullptr;
     pl->items = nullptr;
@@ -301,7 +299,7 @@ static int ensure_capacity(Plan *pl, int64_t n) {
     PMMM_HIP(hipMalloc(&pl->sorted, 4 * pl->tsize * n));
     PMMM_HIP(hipMalloc(&pl->pos, sizeof(int) * n));
     PMMM_HIP(hipMalloc(&pl->staged, 4 * pl->tsize * n));
-    PMMM_HIP(hipMalloc(&pl->tile_row, sizeof(int) * near_tile_capacity(n, pl->n)));
+    PMMM_HIP(hipMalloc(&pl->lists, sizeof(int) * near_list_ints(n, pl->n)));
     PMMM_HIP(hipMalloc(&pl->count, sizeof(int) * bin_hist_ints(n)));
     PMMM_HIP(hipMalloc(&pl->tile_sums, sizeof(int) * bin_scan_tiles(n)));
     PMMM_HIP(hipMalloc(&pl->items, sizeof(int4) * dense_items_cap(n, pl->K)));
@@ -331,7 +329,6 @@ static void destroy(Plan *pl) {
     hipFree(pl->L);
     hipFree(pl->start);
     hipFree(pl->small);
-    hipFree(pl->tile_first);
     hipFree(pl->sums);
     hipFree(pl->qr2_partial);
     hipFree(pl->mM);
@@ -371,9 +368,9 @@ static int alloc_plan(Plan *pl, hipStream_t s) {
     PMMM_HIP(hipMalloc(&pl->M, (size_t)(pl->P + 1) * pl->K * t));
     PMMM_HIP(hipMalloc(&pl->L, (size_t)pl->P * pl->K * t));
     PMMM_HIP(hipMalloc(&pl->start, sizeof(int) * (pl->K + 1)));
-    // [0] dense items, [1] domain flag, [2] near tiles, [3] partial slots
+    // [0] dense items, [1] domain flag, [3] partial slots,
+    // [4] split cells, [5..7] near-field lists
     PMMM_HIP(hipMalloc(&pl->small, sizeof(int) * 8));
-    PMMM_HIP(hipMalloc(&pl->tile_first, sizeof(int) * (size_t)pl->n * pl->n));
     PMMM_HIP(hipMalloc(&pl->sums, sizeof(double) * 8));
     PMMM_HIP(hipMalloc(&pl->qr2_partial, sizeof(double) * pl->n));
     PMMM_HIP(hipMemsetAsync(pl->small, 0, sizeof(int) * 8, s));
@@ -400,7 +397,7 @@ enum CallMode { kFar = 0, kNear = 1, kTotal = 2, kHierFine = 3, kHierTotal = 4 }
 // Per-particle device buffers of one call: the plan's own (grown on demand)
 // or, for the allocation-free entry point, slices of the static scratch.
 struct PBuf {
-    int *cell_of, *slot, *perm, *scell, *pos, *tile_row, *count, *tile_sums;
+    int *cell_of, *slot, *perm, *scell, *pos, *lists, *count, *tile_sums;
     void *sorted, *staged;
     int4 *items;
     float *partial;
@@ -409,7 +406,7 @@ struct PBuf {
 
 static PBuf plan_pbuf(const Plan *pl) {
     return PBuf{pl->cell_of,    pl->slot,   pl->perm,   pl->scell,
-                pl->pos,        pl->tile_row, pl->count, pl->tile_sums,
+                pl->pos,        pl->lists,  pl->count,  pl->tile_sums,
                 pl->sorted,     pl->staged, pl->items,  pl->partial,
                 dense_items_cap(pl->cap, pl->K), dense_slots_cap(pl->cap)};
 }
@@ -627,9 +624,8 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
         a.scell = pb.scell;
         a.sorted = pb.sorted;
         a.inv_h = pl->inv_h;
-        a.tile_first = pl->tile_first;
-        a.tile_row = pb.tile_row;
-        a.ntiles = pl->small + 2;
+        a.lists = pb.lists;
+        a.small = pl->small;
         a.staged = pb.staged;
         PMMM_HIP(launch_near<T>(a, s));
         PMMM_HIP(launch_unpermute<T>(n, pb.pos, pb.staged, phi, gx, gy, gz,
@@ -726,7 +722,7 @@ static int far_noalloc(pmmm_plan_s *pl, int64_t n, const float *x, const float *
                            kNoAllocSums + kNoAllocItems);
     pb.items_cap = kNoAllocItemsCap;
     pb.slots_cap = kNoAllocSlotsCap;
-    pb.tile_row = nullptr;  // far field only
+    pb.lists = nullptr;  // far field only
     if ((size_t)bin_hist_ints(n) * sizeof(int) > kNoAllocHist ||
         (size_t)bin_scan_tiles(n) * sizeof(int) > kNoAllocSums) {
         set_error("radix-sort scratch exceeds the static array");

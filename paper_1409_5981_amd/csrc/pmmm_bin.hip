@@ -97,10 +97,11 @@ __global__ void __launch_bounds__(1024) k_rb_hist(
     for (int d = threadIdx.x; d < nb; d += blockDim.x) s_hist[d] = 0;
     if (first && t == 0 && threadIdx.x == 0) {
         // item, partial-slot and split-cell counts of this binning (filled by
-        // k_rb_bounds)
+        // k_rb_bounds), and the near field's list counts
         small[(int64_t)blockIdx.y * 8] = 0;
         small[(int64_t)blockIdx.y * 8 + 3] = 0;
         small[(int64_t)blockIdx.y * 8 + 4] = 0;
+        for (int k = 5; k < 8; ++k) small[(int64_t)blockIdx.y * 8 + k] = 0;
     }
     __syncthreads();
     int kv[R];

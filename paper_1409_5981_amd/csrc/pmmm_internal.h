@@ -726,13 +726,14 @@ struct NearArgs {
     const int *start, *scell;
     const void *sorted;
     double inv_h;
-    int *tile_first, *tile_row, *ntiles;  // [ncell^2], [near_tile_capacity], [1] scratch
+    int *lists;                     // [near_list_ints(n, ncell)] work lists
+    int *small;                     // [5..7]: counts of the lists, zeroed by the binning
     void *staged;                   // out4<T>[n] sorted-order results
 };
 template <typename T>
 hipError_t launch_near(const NearArgs &a, hipStream_t s);
-// Upper bound of the near-field tiles of n particles on ncell^3 cells.
-int64_t near_tile_capacity(int64_t n, int ncell);
+// Ints of the near field's work lists for n particles on ncell^3 cells.
+int64_t near_list_ints(int64_t n, int ncell);
 // p[0 .. count) = 0 with a fill kernel.
 hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s);
 

@@ -151,3 +151,50 @@ def test_total_plummer_vs_direct_sum():
     print(f"open Plummer 2^22 64^3 p=6 c=2 FP32: method error vs direct sum: "
           f"grad {eg:.3e} phi {ep:.3e} (worst-case bound {_errest(2, 6):.1e})")
     assert eg < _errest(2, 6) and ep < _errest(2, 6)
+
+
+@pytest.mark.parametrize("prec,dt", [("f32", np.float32), ("f64", np.float64)])
+@pytest.mark.parametrize("boundary,n_cells,cutoff", [
+    ("periodic", 8, 2), ("periodic", 5, 2), ("periodic", 7, 1), ("open", 8, 1)])
+def test_near_cell_occupancies(prec, dt, boundary, n_cells, cutoff):
+    """The ways a row of cells is worked on, side by side on one mesh: cells
+    of 0, 1, 2, 3, an odd number, and one below, at and above the targets of a
+    piece and of two pieces; rows of a few particles per cell; rows of almost
+    none; empty rows.  Periodic ranges wrap at both ends."""
+    rng = np.random.default_rng(63)
+    crowded = [129, 0, 1, 2, 64, 3, 63, 65]
+    light = [5, 4, 6, 3, 7, 0, 5, 4]
+    cell, pos = [], []
+    for row in range(n_cells * n_cells):
+        kind = row % 5
+        for x in range(n_cells):
+            k = (crowded[(x + row) % 8] if kind == 0 and row % 15 == 0 else
+                 light[x] if kind in (1, 2) else
+                 1 if kind == 3 and x % 4 == 0 else 0)
+            for _ in range(k):
+                cell.append((x, row % n_cells, row // n_cells))
+    pos = (np.asarray(cell) + rng.random((len(cell), 3))) / 8.0
+    order = rng.permutation(len(cell))
+    pos = pos[order].astype(dt)
+    edge = dt(n_cells / 8.0)
+    pos = np.where(pos >= edge, np.nextafter(edge, dt(0)), pos)
+    q = rng.standard_normal(len(cell)).astype(dt)
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, n_cells, 3,
+                            boundary, box=float(edge))
+    res, plan = _gpu(ps, prec, "near", cutoff=cutoff)
+    nphi, ng = exact.near(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps, cutoff))
+    assert_parity(res, nphi, ng, prec, f"occupancies {boundary} n={n_cells} c={cutoff} {prec}")
+    again, _ = _gpu(ps, prec, "near", plan=plan)
+    assert all(np.array_equal(res[k], again[k]) for k in res)   # list order decides no sum
+
+
+@pytest.mark.parametrize("prec,dt", [("f32", np.float32), ("f64", np.float64)])
+@pytest.mark.parametrize("n", [40, 4000])
+def test_near_coincident_particles(prec, dt, n):
+    """Two particles at one position give the infinite potential the sum has,
+    in sparse rows (n = 40) and crowded cells alike; the others stay finite."""
+    ps = _set(n, 4, 3, "open", 64, dt, neutral=False)
+    ps.x[7], ps.y[7], ps.z[7] = ps.x[30], ps.y[30], ps.z[30]
+    res, _ = _gpu(ps, prec, "near", cutoff=1)
+    inf = np.isinf(res["phi"])
+    assert inf[7] and inf[30] and inf.sum() == 2
