@@ -39,6 +39,11 @@ int hip_fail(hipError_t e, const char *what) {
 // particles, one wave each.
 static int dense_threshold_for(int group) { return 16 * group; }
 
+// Up to this many particles a dense cell is one work item, reduced by one block
+// (64 x 512 particles for its four waves at worst), so that no launch adds
+// partial sums: 2 us of a call of 40.
+constexpr int64_t kWholeCellMaxN = int64_t(1) << 15;
+
 // From this many particles on, L2P writes its results in sorted order and a
 // second kernel sends them back to the caller's order (fewer, wider random
 // accesses); below it the extra launch costs more than it saves.
@@ -257,8 +262,8 @@ static size_t plan_bytes(const Plan *pl) {
 
 static size_t particle_bytes(const Plan *pl, int64_t n) {
     return (size_t)n * (5 * sizeof(int) + 8 * pl->tsize) +
-           sizeof(int) * (size_t)(near_list_ints(n, pl->n) + bin_hist_ints(n) +
-                                  bin_scan_tiles(n)) +
+           sizeof(int) * (size_t)(near_list_ints(n, pl->n) + bin_hist_ints(n, pl->K) +
+                                  bin_scan_tiles(n, pl->K)) +
            sizeof(int4) * (size_t)dense_items_cap(n, pl->K) +
            sizeof(float) * (size_t)dense_slots_cap(n) * (pl->P + 1);
 }
@@ -300,8 +305,8 @@ static int ensure_capacity(Plan *pl, int64_t n) {
     PMMM_HIP(hipMalloc(&pl->pos, sizeof(int) * n));
     PMMM_HIP(hipMalloc(&pl->staged, 4 * pl->tsize * n));
     PMMM_HIP(hipMalloc(&pl->lists, sizeof(int) * near_list_ints(n, pl->n)));
-    PMMM_HIP(hipMalloc(&pl->count, sizeof(int) * bin_hist_ints(n)));
-    PMMM_HIP(hipMalloc(&pl->tile_sums, sizeof(int) * bin_scan_tiles(n)));
+    PMMM_HIP(hipMalloc(&pl->count, sizeof(int) * bin_hist_ints(n, pl->K)));
+    PMMM_HIP(hipMalloc(&pl->tile_sums, sizeof(int) * bin_scan_tiles(n, pl->K)));
     PMMM_HIP(hipMalloc(&pl->items, sizeof(int4) * dense_items_cap(n, pl->K)));
     PMMM_HIP(hipMalloc(&pl->partial, sizeof(float) * dense_slots_cap(n) * (pl->P + 1)));
     pl->cap = n;
@@ -500,6 +505,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
     const bool sorted_stage = mode == kNear || mode == kTotal || mode == kHierTotal;
     const int group = pl->tune_group > 0 ? pl->tune_group : group_for((double)n / (double)pl->K);
     const int dense_thr = dense_threshold_for(group);
+    const int whole = n <= kWholeCellMaxN;
 
     {
         StageTimer t(pl, PMMM_STAGE_BIN, s, timed);
@@ -521,12 +527,13 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
         b.perm = pb.perm;
         b.flag = pl->small + 1;
         b.items = mode != kNear ? pb.items : nullptr;
+        b.whole = whole;
         b.items_cap = pb.items_cap;
         b.slots_cap = pb.slots_cap;
+        b.dense_threshold = dense_thr;
         b.small = pl->small;
         b.pos = sorted_stage ? pb.pos : nullptr;
         b.tile_sums = pb.tile_sums;
-        b.dense_threshold = dense_thr;
         b.sorted = pb.sorted;
         b.recs = pb.staged;   // free until L2P
         PMMM_HIP(launch_bin<T>(b, s));
@@ -541,6 +548,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
             m.start = pl->start;
             m.dense_threshold = dense_thr;
             m.items = pb.items;
+            m.whole = whole;
             m.items_cap = pb.items_cap;
             m.small = pl->small;
             m.partial = pb.partial;
@@ -646,8 +654,10 @@ constexpr int64_t kNoAllocMaxN = PMMM_NOALLOC_MAX_N;
 constexpr size_t kNoAllocInts = (size_t)kNoAllocMaxN * sizeof(int);
 constexpr size_t kNoAllocRecs = (size_t)kNoAllocMaxN * sizeof(particle4<float>);
 // radix-sort histograms (512 buckets per tile) and their scan scratch
-constexpr size_t kNoAllocHist = (size_t)bin_hist_ints(kNoAllocMaxN) * sizeof(int);
-constexpr size_t kNoAllocSums = ((size_t)bin_scan_tiles(kNoAllocMaxN) * sizeof(int) + 255) / 256 * 256;
+constexpr int64_t kNoAllocMaxK = int64_t(1) << 18;   // cells of an FP32 plan at most
+constexpr size_t kNoAllocHist = (size_t)bin_hist_ints(kNoAllocMaxN, kNoAllocMaxK) * sizeof(int);
+constexpr size_t kNoAllocSums =
+    ((size_t)bin_scan_tiles(kNoAllocMaxN, kNoAllocMaxK) * sizeof(int) + 255) / 256 * 256;
 // dense items: at most max_n / (threshold + 1) dense cells whatever the mesh
 constexpr int64_t kNoAllocItemsCap = dense_items_cap(kNoAllocMaxN, kNoAllocMaxN);
 constexpr int64_t kNoAllocSlotsCap = dense_slots_cap(kNoAllocMaxN);
@@ -723,8 +733,8 @@ static int far_noalloc(pmmm_plan_s *pl, int64_t n, const float *x, const float *
     pb.items_cap = kNoAllocItemsCap;
     pb.slots_cap = kNoAllocSlotsCap;
     pb.lists = nullptr;  // far field only
-    if ((size_t)bin_hist_ints(n) * sizeof(int) > kNoAllocHist ||
-        (size_t)bin_scan_tiles(n) * sizeof(int) > kNoAllocSums) {
+    if ((size_t)bin_hist_ints(n, pl->K) * sizeof(int) > kNoAllocHist ||
+        (size_t)bin_scan_tiles(n, pl->K) * sizeof(int) > kNoAllocSums) {
         set_error("radix-sort scratch exceeds the static array");
         return PMMM_EINVAL;
     }
@@ -817,7 +827,6 @@ static int multi_impl(pmmm_plan_s *pl, int64_t n, const float *x, const float *y
         b.scell = pl->scell;
         b.perm = pl->perm;
         b.flag = pl->small + 1;
-        b.items = nullptr;        // the multi-charge P2M reduces every cell itself
         b.small = pl->small;
         b.tile_sums = pl->tile_sums;
         b.sorted = pl->sorted;
@@ -1097,6 +1106,7 @@ static int class_enqueue(pmmm_batch_s *b, BatchClass &c, const float *x, const f
         const int ns = (int)c.members.size();
         const int group = group_for((double)c.tot_np / ((double)pl->K * ns));
         const int dense_thr = dense_threshold_for(group);
+        const int whole = c.max_np <= kWholeCellMaxN;
         BinArgs bn{};
         bn.n = 0;
         bn.x = x;
@@ -1115,11 +1125,12 @@ static int class_enqueue(pmmm_batch_s *b, BatchClass &c, const float *x, const f
         bn.perm = b->perm;
         bn.flag = b->flag;
         bn.items = c.items;
+        bn.whole = whole;
         bn.items_cap = c.items_cap;
         bn.slots_cap = c.slots_cap;
+        bn.dense_threshold = dense_thr;
         bn.small = c.small;
         bn.tile_sums = c.tile_sums;
-        bn.dense_threshold = dense_thr;
         bn.sorted = b->sorted;
         bn.recs = b->recs;
         bn.prange = c.d_prange;
@@ -1133,6 +1144,7 @@ static int class_enqueue(pmmm_batch_s *b, BatchClass &c, const float *x, const f
         m.start = c.start;
         m.dense_threshold = dense_thr;
         m.items = c.items;
+        m.whole = whole;
         m.items_cap = c.items_cap;
         m.small = c.small;
         m.partial = c.partial;
@@ -1284,7 +1296,7 @@ static int batch_far(pmmm_batch_s *b, const int64_t *offsets, const float *x, co
             PMMM_HIP(hipMemcpyAsync(c.d_prange, h, sizeof(int64_t) * 2 * c.members.size(),
                                     hipMemcpyHostToDevice, s));
             PMMM_HIP(hipStreamSynchronize(s));
-            if (c.count == nullptr || bin_hist_ints(c.max_np) > bin_hist_ints(c.hist_cap)) {
+            if (c.count == nullptr || c.max_np > c.hist_cap) {
                 // radix-sort scratch for the largest system of the class
                 const size_t ns = c.members.size();
                 hipFree(c.count);
@@ -1297,8 +1309,8 @@ static int batch_far(pmmm_batch_s *b, const int64_t *offsets, const float *x, co
                 c.hist_cap = -1;
                 const int64_t ic = dense_items_cap(c.max_np, c.plan->K);
                 const int64_t sc = dense_slots_cap(c.max_np);
-                PMMM_HIP(hipMalloc(&c.count, sizeof(int) * bin_hist_ints(c.max_np) * ns));
-                PMMM_HIP(hipMalloc(&c.tile_sums, sizeof(int) * bin_scan_tiles(c.max_np) * ns));
+                PMMM_HIP(hipMalloc(&c.count, sizeof(int) * bin_hist_ints(c.max_np, c.plan->K) * ns));
+                PMMM_HIP(hipMalloc(&c.tile_sums, sizeof(int) * bin_scan_tiles(c.max_np, c.plan->K) * ns));
                 PMMM_HIP(hipMalloc(&c.items, sizeof(int4) * ic * ns));
                 PMMM_HIP(hipMalloc(&c.partial, sizeof(float) * sc * (c.plan->P + 1) * ns));
                 c.items_cap = ic;

@@ -1,40 +1,42 @@
 // Cell binning (Sec. 2.1 requires that the particles of every cell be known,
-// which takes linear time): a stable sort of the particles by cell index, as
-// a least-significant-digit radix sort with digits of at most 9 bits, so the
-// particles of a cell keep the caller's order and every result is bitwise
-// reproducible (no atomics decide an order).  Each pass carries the key (cell),
-// the value (caller index) and the particle record, so no pass gathers.
-//   k_rb_hist     tile histogram of one digit; the first pass computes the
-//                 cells from the positions (and flags open-boundary particles
-//                 outside the box)
+// which takes linear time): a stable sort of the particles by cell index, so
+// the particles of a cell keep the caller's order and every result is bitwise
+// reproducible (no atomics decide an order).  The cell index is cut in two: a
+// partition by its high bits, then a sort of every bucket by the low bits.
+//   k_rb_hist     tile histogram of the high bits, computed from the positions
+//                 (and flags open-boundary particles outside the box)
 //   k_rb_scan1 or k_rb_scan_sums + k_rb_scan
 //                 exclusive scan of the histograms in bucket-major order (so
-//                 tile t's bucket-d elements start after every smaller digit
+//                 tile t's bucket-d elements start after every smaller bucket
 //                 and after bucket d of the tiles before t)
-//   k_rb_scatter  stable scatter of one digit: each wave ranks a contiguous
-//                 chunk of the tile (wave ballots for equal digits plus the
-//                 wave's running count per digit), one prefix over the waves
-//                 per tile, then the tile is put in digit order in LDS and
-//                 written out in runs; the first pass builds the keys and
-//                 records from the positions, the last writes the sorted cell,
-//                 the permutation, the sorted records and, on request, each
-//                 particle's sorted slot
-//   k_rb_bounds   start of every cell by binary search among the sorted slots
-//                 of its last digit, and the P2M work items of the cells
-//                 above the dense threshold (kDenseItem particles each)
+//   k_rb_scatter  stable partition: each wave ranks a contiguous chunk of the
+//                 tile (wave ballots for equal digits plus the wave's running
+//                 count per digit), one prefix over the waves per tile, then
+//                 the tile is put in digit order in LDS and written out in
+//                 runs (key, caller index, particle record)
+//   k_rb_hist2    histograms of the low bits for the chunks of buckets above
+//                 kLocalTile particles (clustered input; other blocks leave)
+//   k_rb_local    sorts a bucket, or one chunk of a large one, by the low bits
+//                 into its final place: sorted cell, permutation, records and,
+//                 on request, each particle's sorted slot; the bucket's
+//                 histogram is also the starts of its cells and lists the P2M
+//                 work items of the cells above the dense threshold
+//   k_bin_keys, k_bin_small   all of it in two launches, for few particles and
+//                 cells
 // Cell index: I = floor(r n / b) per axis, clamped to [0, n-1]; periodic
 // positions are first wrapped into the box (in cell units).
 //
 // Batches: blockIdx.y selects one of several independent systems on meshes of
 // the same size; prange[2s], prange[2s+1] bound system s's particles in the
 // caller's arrays (null: one system, particles [0, n)), and its per-system
-// arrays sit at fixed strides (start K + 1, items items_cap, small 8,
-// histograms bin_hist_ints(max_np), scan sums bin_scan_tiles(max_np)).
+// arrays sit at fixed strides (start K + 1, small 8, histograms
+// bin_hist_ints(max_np, K), scan sums bin_scan_tiles(max_np, K)).
 #include "pmmm_internal.h"
 
 namespace pmmm {
 
-constexpr int kRadixBuckets = 1 << kRadixMaxBits;
+constexpr int kRadixBuckets = 1 << kRadixMaxBits;   // k_rb_hist, k_rb_scatter
+constexpr int kLocalBuckets = 1 << kLocalMaxBits;   // k_rb_hist2, k_rb_local
 constexpr int kScanOneBlock = 16384;   // histograms up to this size: one-block scan
 
 template <typename T>
@@ -74,81 +76,118 @@ constexpr size_t scatter_lds(int bits) {
     return scatter_region<T, R>(bits) + (size_t)(2 * (1 << bits) + 16) * sizeof(int);
 }
 
-__global__ void k_rb_reset_items(int nsys, int *__restrict__ small) {
-    for (int sy = threadIdx.x; sy < nsys; sy += blockDim.x) {
-        small[(int64_t)sy * 8] = 0;
-        small[(int64_t)sy * 8 + 3] = 0;
-        small[(int64_t)sy * 8 + 4] = 0;
-    }
+// Counts of one system's binning, written by its first kernel: dense P2M
+// items, partial slots and split cells, and the near field's work lists.
+__device__ __forceinline__ void reset_counts(int *__restrict__ small) {
+    small[0] = 0;
+    for (int k = 3; k < 8; ++k) small[k] = 0;
 }
 
-// Tile histogram of digit (key >> shift) & (2^bits - 1), written to
-// hist[d * tiles + t] (every block writes all 2^bits of its entries).
+// Every system empty: zero starts and counts.
+__global__ void __launch_bounds__(256) k_bin_empty(int K, int *__restrict__ start,
+                                                   int *__restrict__ small) {
+    const int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c <= K) start[(int64_t)blockIdx.y * (K + 1) + c] = 0;
+    if (c == 0) reset_counts(small + (int64_t)blockIdx.y * 8);
+}
+
+// Cell of particle i and its record.
+template <typename T>
+__device__ __forceinline__ int cell_record(const T *__restrict__ x, const T *__restrict__ y,
+                                           const T *__restrict__ z, const T *__restrict__ q,
+                                           int64_t i, T inv_h, int nc, int periodic,
+                                           particle4<T> &rec) {
+    int ix, iy, iz, out = 0;
+    cell_coord(x[i], inv_h, nc, nc, periodic, ix, rec.ux, out);
+    cell_coord(y[i], inv_h, nc, nc, periodic, iy, rec.uy, out);
+    cell_coord(z[i], inv_h, nc, nc, periodic, iz, rec.uz, out);
+    rec.q = q != nullptr ? q[i] : T(0);
+    return (iz * nc + iy) * nc + ix;
+}
+
+// Lanes of the wave that are active and hold the same digit d.
+__device__ __forceinline__ uint64_t digit_peers(bool act, int d, int bits) {
+    uint64_t peers = __ballot(act);
+    for (int b = 0; b < bits; ++b) {
+        const uint64_t m = __ballot(act && ((d >> b) & 1));
+        peers &= ((d >> b) & 1) ? m : ~m;
+    }
+    return peers;
+}
+
+// Tile histogram of the bucket key >> shift, written to hist[d * tiles + t]
+// (every block writes all 2^bits of its entries).
 template <typename T, int R>
 __global__ void __launch_bounds__(1024) k_rb_hist(
-    const int64_t *__restrict__ prange, int64_t n, int first, const T *__restrict__ x,
+    const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
     const T *__restrict__ y, const T *__restrict__ z, T inv_h, int nc, int3 lim, int periodic,
-    const int *__restrict__ keys, int *__restrict__ hist, int64_t hist_ints, int tiles,
-    int shift, int bits, int *__restrict__ flag, int *__restrict__ small) {
+    int *__restrict__ hist, int64_t hist_ints, int tiles, int shift, int bits,
+    int *__restrict__ flag, int *__restrict__ small) {
     __shared__ int s_hist[kRadixBuckets];
     int64_t p0, np;
     sys_range(prange, n, p0, np);
     const int nb = 1 << bits, t = blockIdx.x;
     for (int d = threadIdx.x; d < nb; d += blockDim.x) s_hist[d] = 0;
-    if (first && t == 0 && threadIdx.x == 0) {
-        // item, partial-slot and split-cell counts of this binning (filled by
-        // k_rb_bounds), and the near field's list counts
-        small[(int64_t)blockIdx.y * 8] = 0;
-        small[(int64_t)blockIdx.y * 8 + 3] = 0;
-        small[(int64_t)blockIdx.y * 8 + 4] = 0;
-        for (int k = 5; k < 8; ++k) small[(int64_t)blockIdx.y * 8 + k] = 0;
-    }
+    if (t == 0 && threadIdx.x == 0) reset_counts(small + (int64_t)blockIdx.y * 8);
     __syncthreads();
     int kv[R];
     int out = 0;
-    if (first) {
-        T xv[R], yv[R], zv[R];
+    T xv[R], yv[R], zv[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
-            const int64_t i = p0 + (j < np ? j : 0);
-            const bool act = j < np;
-            xv[r] = act ? x[i] : T(0);
-            yv[r] = act ? y[i] : T(0);
-            zv[r] = act ? z[i] : T(0);
-        }
+    for (int r = 0; r < R; ++r) {
+        const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
+        const int64_t i = p0 + (j < np ? j : 0);
+        const bool act = j < np;
+        xv[r] = act ? x[i] : T(0);
+        yv[r] = act ? y[i] : T(0);
+        zv[r] = act ? z[i] : T(0);
+    }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
-            int ix, iy, iz;
-            T u;
-            cell_coord(xv[r], inv_h, nc, lim.x, periodic, ix, u, out);
-            cell_coord(yv[r], inv_h, nc, lim.y, periodic, iy, u, out);
-            cell_coord(zv[r], inv_h, nc, lim.z, periodic, iz, u, out);
-            kv[r] = j < np ? (iz * nc + iy) * nc + ix : -1;
-        }
-        if (out && np > 0) {
-            // only lanes with particles can be outside (inactive lanes read 0)
-            *flag = 1;
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
-            kv[r] = j < np ? keys[p0 + j] : -1;
-        }
+    for (int r = 0; r < R; ++r) {
+        const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
+        int ix, iy, iz;
+        T u;
+        cell_coord(xv[r], inv_h, nc, lim.x, periodic, ix, u, out);
+        cell_coord(yv[r], inv_h, nc, lim.y, periodic, iy, u, out);
+        cell_coord(zv[r], inv_h, nc, lim.z, periodic, iz, u, out);
+        kv[r] = j < np ? (iz * nc + iy) * nc + ix : -1;
+    }
+    if (out && np > 0) {
+        // only lanes with particles can be outside (inactive lanes read 0)
+        *flag = 1;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
-        if (kv[r] >= 0) atomicAdd(&s_hist[(kv[r] >> shift) & (nb - 1)], 1);
+        if (kv[r] >= 0) atomicAdd(&s_hist[kv[r] >> shift], 1);
     __syncthreads();
     int *h = hist + (int64_t)blockIdx.y * hist_ints;
     for (int d = threadIdx.x; d < nb; d += blockDim.x) h[(int64_t)d * tiles + t] = s_hist[d];
 }
 
+// Scanned values of the entries base .. base + C - 1 (the first is run), and
+// the bucket starts -- the entries of tile 0 -- once more in a row behind the
+// histogram, where every block of the local sort reads them all.
+template <int C>
+__device__ __forceinline__ void put_scanned(int *__restrict__ hist, int64_t base, int64_t L,
+                                            int tiles, int run, const int *v) {
+    int b = (int)(base / tiles), t = (int)(base - (int64_t)b * tiles);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+        if (base + k < L) {
+            hist[base + k] = run;
+            if (t == 0) hist[L + b] = run;
+        }
+        run += v[k];
+        if (++t == tiles) {
+            t = 0;
+            ++b;
+        }
+    }
+}
+
 // Exclusive scan of the L (<= kScanOneBlock) histogram entries of every
 // system in one block: 16 consecutive entries per thread.
-__global__ void __launch_bounds__(1024) k_rb_scan1(int64_t L, int64_t hist_ints,
+__global__ void __launch_bounds__(1024) k_rb_scan1(int64_t L, int64_t hist_ints, int tiles,
                                                    int *__restrict__ hist) {
     __shared__ int wtot[16];
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -171,11 +210,7 @@ __global__ void __launch_bounds__(1024) k_rb_scan1(int64_t L, int64_t hist_ints,
     __syncthreads();
     int run = inc - tot;
     for (int w = 0; w < wid; ++w) run += wtot[w];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        if (base + k < L) hist[base + k] = run;
-        run += v[k];
-    }
+    put_scanned<16>(hist, base, L, tiles, run, v);
 }
 
 // The same for larger histograms, in scan tiles of 4096: per-tile sums, then
@@ -203,7 +238,7 @@ __global__ void __launch_bounds__(1024) k_rb_scan_sums(int64_t L, int64_t hist_i
     }
 }
 
-__global__ void __launch_bounds__(1024) k_rb_scan(int64_t L, int64_t hist_ints,
+__global__ void __launch_bounds__(1024) k_rb_scan(int64_t L, int64_t hist_ints, int tiles,
                                                   int *__restrict__ hist,
                                                   const int *__restrict__ sums) {
     __shared__ int wtot[16];
@@ -238,23 +273,41 @@ __global__ void __launch_bounds__(1024) k_rb_scan(int64_t L, int64_t hist_ints,
     __syncthreads();
     int run = pre_s + inc - tot;
     for (int w = 0; w < wid; ++w) run += wtot[w];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (base + k < L) hist[base + k] = run;
-        run += v[k];
+    put_scanned<4>(hist, base, L, tiles, run, v);
+}
+
+// P2M items of a dense cell of cnt particles: J = ceil(cnt / kDenseItem) items
+// {cell, j, J, first partial slot (J > 1) or -1}, a cell of J > 1 also as split
+// {cell, J, first slot}; or (whole) one item for the cell.  Places are reserved with atomics, so they vary from
+// call to call, but every item covers a fixed particle range and the partials
+// of a cell are added in a fixed order, so the moments do not.
+__device__ __forceinline__ void list_dense(int cell, int cnt, int whole, int4 *__restrict__ items,
+                                           int64_t items_cap, int64_t splits_cap,
+                                           int *__restrict__ small) {
+    const int J = whole ? 1 : (cnt + kDenseItem - 1) / kDenseItem;
+    const int base = atomicAdd(small, J);
+    const int ps = J > 1 ? atomicAdd(small + 3, J) : -1;
+    for (int j = 0; j < J; ++j)
+        if (base + j < items_cap - splits_cap) items[base + j] = int4{cell, j, J, ps};
+    if (J > 1) {
+        const int si = atomicAdd(small + 4, 1);
+        if (si < splits_cap) items[items_cap - splits_cap + si] = int4{cell, J, ps, 0};
     }
 }
 
-// Stable scatter of one digit over tiles of 1024 R elements; wave w ranks
-// elements [64 R w, 64 R (w + 1)) of its tile, 64 at a time.
+// Stable partition by the bucket over tiles of 1024 R elements; wave w ranks
+// elements [64 R w, 64 R (w + 1)) of its tile, 64 at a time.  With start the
+// buckets are the cells (few cells): the partition is the whole sort, and tile
+// 0 writes the starts and lists the dense cells as k_rb_local does.
 template <typename T, int R>
 __global__ void __launch_bounds__(1024) k_rb_scatter(
-    const int64_t *__restrict__ prange, int64_t n, int first, int last, const T *__restrict__ x,
+    const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
     const T *__restrict__ y, const T *__restrict__ z, const T *__restrict__ q, T inv_h, int nc,
-    int periodic, const int *__restrict__ keys_in, const int *__restrict__ vals_in,
-    const particle4<T> *__restrict__ recs_in, int *__restrict__ keys_out,
-    int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out, int *__restrict__ pos,
-    const int *__restrict__ offs, int64_t hist_ints, int tiles, int shift, int bits) {
+    int periodic, int *__restrict__ keys_out, int *__restrict__ vals_out,
+    particle4<T> *__restrict__ recs_out, const int *__restrict__ offs, int64_t hist_ints,
+    int tiles, int shift, int bits, int K, int *__restrict__ pos, int *__restrict__ start,
+    int dense_thr, int whole, int4 *__restrict__ items, int64_t items_cap, int64_t splits_cap,
+    int *__restrict__ small) {
     constexpr int TILE = 1024 * R;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nb = 1 << bits;
@@ -272,6 +325,17 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
     const int64_t t0 = (int64_t)t * TILE;
     const int na = (int)(np - t0 <= 0 ? 0 : (np - t0 > TILE ? TILE : np - t0));
     for (int e = tid; e < 16 * nb; e += 1024) wcnt[e] = 0;
+    if (start != nullptr && t == 0) {
+        int *st = start + (int64_t)blockIdx.y * (K + 1);
+        for (int d = tid; d <= K; d += 1024) {
+            const int s0 = d < nb ? offs[(int64_t)d * tiles] : (int)np;
+            const int s1 = d + 1 < nb ? offs[(int64_t)(d + 1) * tiles] : (int)np;
+            st[d] = s0;
+            if (d < K && items != nullptr && s1 - s0 > dense_thr)
+                list_dense(d, s1 - s0, whole, items + (int64_t)blockIdx.y * items_cap, items_cap,
+                           splits_cap, small + (int64_t)blockIdx.y * 8);
+        }
+    }
 
     int key[R], val[R], dig[R];
     particle4<T> rec[R];
@@ -280,25 +344,14 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
         const int e = wid * 64 * R + r * 64 + lane;
         const int64_t i = p0 + t0 + (e < na ? e : 0);
         if (e < na) {
-            if (first) {
-                int ix, iy, iz, out = 0;
-                cell_coord(x[i], inv_h, nc, nc, periodic, ix, rec[r].ux, out);
-                cell_coord(y[i], inv_h, nc, nc, periodic, iy, rec[r].uy, out);
-                cell_coord(z[i], inv_h, nc, nc, periodic, iz, rec[r].uz, out);
-                rec[r].q = q != nullptr ? q[i] : T(0);
-                key[r] = (iz * nc + iy) * nc + ix;
-                val[r] = (int)i;
-            } else {
-                key[r] = keys_in[i];
-                val[r] = vals_in[i];
-                rec[r] = recs_in[i];
-            }
+            key[r] = cell_record(x, y, z, q, i, inv_h, nc, periodic, rec[r]);
+            val[r] = (int)i;
         } else {
             key[r] = 0;
             val[r] = 0;
             rec[r] = particle4<T>{T(0), T(0), T(0), T(0)};
         }
-        dig[r] = (key[r] >> shift) & (nb - 1);
+        dig[r] = key[r] >> shift;
     }
     __syncthreads();
 
@@ -313,11 +366,7 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
         const int e = wid * 64 * R + r * 64 + lane;
         const bool act = e < na;
         const int d = dig[r];
-        uint64_t peers = __ballot(act);
-        for (int b = 0; b < bits; ++b) {
-            const uint64_t m = __ballot(act && ((d >> b) & 1));
-            peers &= ((d >> b) & 1) ? m : ~m;
-        }
+        const uint64_t peers = digit_peers(act, d, bits);
         const int before = __popcll(peers & lt);
         const int base = act ? wcnt[wid * nb + d] : 0;
         __builtin_amdgcn_wave_barrier();
@@ -327,18 +376,26 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
     }
     __syncthreads();
 
-    // per digit: exclusive prefix over the waves (in place) and the tile count
-    int tot = 0;
-    if (tid < nb) {
+    // per digit: exclusive prefix over the waves (in place) and the tile count;
+    // thread tid holds the digits [tid DP, tid DP + DP)
+    constexpr int DP = kRadixBuckets / 1024;
+    int tot[DP], sum = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const int c = wcnt[w * nb + tid];
-            wcnt[w * nb + tid] = tot;
-            tot += c;
+    for (int u = 0; u < DP; ++u) {
+        const int d = tid * DP + u;
+        tot[u] = 0;
+        if (d < nb) {
+#pragma unroll
+            for (int w = 0; w < 16; ++w) {
+                const int c = wcnt[w * nb + d];
+                wcnt[w * nb + d] = tot[u];
+                tot[u] += c;
+            }
         }
+        sum += tot[u];
     }
     // exclusive scan of the tile counts over the digits
-    int inc = tot;
+    int inc = sum;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int u = __shfl_up(inc, off, 64);
@@ -346,12 +403,16 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
     }
     if (lane == 63) wtot[wid] = inc;
     __syncthreads();
-    if (tid < nb) {
-        int pre = 0;
-        for (int w = 0; w < wid; ++w) pre += wtot[w];
-        const int l = pre + inc - tot;
-        ls[tid] = l;
-        goff[tid] = offs[(int64_t)tid * tiles + t] - l;
+    int l = inc - sum;
+    for (int w = 0; w < wid; ++w) l += wtot[w];
+#pragma unroll
+    for (int u = 0; u < DP; ++u) {
+        const int d = tid * DP + u;
+        if (d < nb) {
+            ls[d] = l;
+            goff[d] = offs[(int64_t)d * tiles + t] - l;
+        }
+        l += tot[u];
     }
     __syncthreads();
     int lidx[R];
@@ -374,7 +435,7 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
         dst[r] = 0;
         if (jj < na) {
             const int k = sint[jj];
-            dst[r] = goff[(k >> shift) & (nb - 1)] + jj;
+            dst[r] = goff[k >> shift] + jj;
             keys_out[p0 + dst[r]] = k;
         }
     }
@@ -389,7 +450,7 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
         if (jj < na) {
             const int v = sint[jj];
             vals_out[p0 + dst[r]] = v;
-            if (last && pos != nullptr) pos[v] = (int)(p0 + dst[r]);
+            if (pos != nullptr) pos[v] = (int)(p0 + dst[r]);
         }
     }
     __syncthreads();
@@ -404,69 +465,385 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
     }
 }
 
-// start[c] = first sorted slot of the system with cell >= c (relative to the
-// system's first particle), c = 0..K, searched among the slots whose last
-// digit equals c's (their range comes from the last pass's scanned
-// histogram).  A cell of more than dense_thr particles becomes J =
-// ceil(count / kDenseItem) P2M items {cell, j, J, first partial slot (J > 1)
-// or -1}, and a cell of J > 1 items is also listed as split {cell, J, first
-// slot}; items, slots and list entries are reserved with atomics, so their
-// positions vary from call to call, but every item covers a fixed particle
-// range and the partials of a cell are added in a fixed order, so the
-// moments do not.
-__global__ void __launch_bounds__(256) k_rb_bounds(
-    const int64_t *__restrict__ prange, int64_t n, int K, const int *__restrict__ skeys,
-    int *__restrict__ start, int dense_thr, int4 *__restrict__ items, int64_t items_cap,
-    int64_t splits_cap, int *__restrict__ small, const int *__restrict__ offs, int64_t hist_ints,
-    int tiles, int shift, int bits) {
+// The chunk of block blk: bucket b of the partition holds the slots [start,
+// start + cnt) and makes J = max(1, ceil(cnt / kLocalTile)) chunks, of which
+// this is chunk j; mbase counts the chunks of the buckets before it that make
+// more than one.  b < 0: no such chunk.  Two barriers; scr: 2 x 16 ints.
+struct Chunk {
+    int b, start, cnt, j, J, mbase;
+};
+__device__ __forceinline__ Chunk find_chunk(int blk, int nb, int64_t np, const int *first_of,
+                                            int *scr, Chunk *found) {
+    constexpr int DP = kRadixBuckets / 1024;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (tid == 0) found->b = -1;
+    int first[DP + 1], js = 0, ms = 0;
+#pragma unroll
+    for (int u = 0; u <= DP; ++u) {
+        const int d = tid * DP + u;
+        first[u] = d < nb ? first_of[d] : (int)np;
+    }
+    int J[DP], M[DP];
+#pragma unroll
+    for (int u = 0; u < DP; ++u) {
+        const int c = (first[u + 1] - first[u] + kLocalTile - 1) / kLocalTile;
+        J[u] = tid * DP + u < nb ? (c > 1 ? c : 1) : 0;
+        M[u] = c > 1 ? c : 0;
+        js += J[u];
+        ms += M[u];
+    }
+    int ji = js, mi = ms;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int a = __shfl_up(ji, off, 64), m = __shfl_up(mi, off, 64);
+        if (lane >= off) {
+            ji += a;
+            mi += m;
+        }
+    }
+    if (lane == 63) {
+        scr[wid] = ji;
+        scr[16 + wid] = mi;
+    }
+    __syncthreads();
+    ji -= js;
+    mi -= ms;
+    for (int w = 0; w < wid; ++w) {
+        ji += scr[w];
+        mi += scr[16 + w];
+    }
+#pragma unroll
+    for (int u = 0; u < DP; ++u) {
+        if (blk >= ji && blk < ji + J[u])
+            *found = Chunk{tid * DP + u, first[u], first[u + 1] - first[u], blk - ji, J[u], mi};
+        ji += J[u];
+        mi += M[u];
+    }
+    __syncthreads();
+    return *found;
+}
+
+// Low-bit histogram of one chunk of a bucket that makes several.
+__global__ void __launch_bounds__(1024) k_rb_hist2(const int64_t *__restrict__ prange, int64_t n,
+                                                   const int *__restrict__ keys,
+                                                   int *__restrict__ hist, int64_t hist_ints,
+                                                   int tiles, int nb, int lbits) {
+    __shared__ int s_hist[kLocalBuckets], scr[32];
+    __shared__ Chunk found;
     int64_t p0, np;
     sys_range(prange, n, p0, np);
+    hist += (int64_t)blockIdx.y * hist_ints;
+    const int *first_of = hist + (int64_t)nb * tiles;
+    const int nl = 1 << lbits, tid = threadIdx.x;
+    int large = 0;                      // any bucket of several chunks?
+    for (int d = tid; d < nb; d += 1024)
+        large |= (d + 1 < nb ? first_of[d + 1] : (int)np) - first_of[d] > kLocalTile;
+    if (!__syncthreads_or(large)) return;
+    const Chunk c = find_chunk(blockIdx.x, nb, np, first_of, scr, &found);
+    if (c.b < 0 || c.J == 1) return;    // the same for every thread
+    for (int d = tid; d < nl; d += 1024) s_hist[d] = 0;
+    __syncthreads();
+    const int e1 = min(c.cnt - c.j * kLocalTile, kLocalTile);
+    const int *k = keys + p0 + c.start + c.j * kLocalTile;
+    for (int e = tid; e < e1; e += 1024) atomicAdd(&s_hist[k[e] & (nl - 1)], 1);
+    __syncthreads();
+    int *h = hist + (int64_t)nb * (tiles + 1) + (int64_t)(c.mbase + c.j) * nl;
+    for (int d = tid; d < nl; d += 1024) h[d] = s_hist[d];
+}
+
+// LDS of the local sort: the per-wave counts [16][nl], later the staging area
+// of the chunk (its records are the largest array).
+template <typename T>
+constexpr size_t local_lds(int lbits) {
+    return ((size_t)16 * sizeof(int) << lbits) > (size_t)kLocalTile * sizeof(particle4<T>)
+               ? ((size_t)16 * sizeof(int) << lbits)
+               : (size_t)kLocalTile * sizeof(particle4<T>);
+}
+
+// Stable sort of one chunk by the low bits of the cell into the final arrays.
+// Wave w takes a contiguous share of the chunk and ranks it as k_rb_scatter
+// does; the chunk is then put in order in LDS and written out in runs -- one
+// run for a bucket of one chunk.  (Storing each element straight to its slot
+// costs an L2 request per element and array: 27 us for 2^20 particles.)
+template <typename T>
+__global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) k_rb_local(
+    const int64_t *__restrict__ prange, int64_t n, int K, const int *__restrict__ keys_in,
+    const int *__restrict__ vals_in, const particle4<T> *__restrict__ recs_in,
+    int *__restrict__ keys_out, int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out,
+    int *__restrict__ pos, int *__restrict__ start, const int *__restrict__ hist,
+    int64_t hist_ints, int tiles, int nb, int lbits, int dense_thr, int whole,
+    int4 *__restrict__ items,
+    int64_t items_cap, int64_t splits_cap, int *__restrict__ small) {
+    constexpr int RM = kLocalTile / 1024;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int scr[32], ls[kLocalBuckets], goff[kLocalBuckets];
+    __shared__ Chunk found;
+    const int nl = 1 << lbits, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    int *wcnt = (int *)lds_raw;                     // [16][nl] while ranking
+    int *sint = (int *)lds_raw;                     // staging: kLocalTile ints
+    particle4<T> *srec = (particle4<T> *)lds_raw;   // staging: kLocalTile records
+    int64_t p0, np;
+    sys_range(prange, n, p0, np);
+    hist += (int64_t)blockIdx.y * hist_ints;
     start += (int64_t)blockIdx.y * (K + 1);
-    if (items != nullptr) items += (int64_t)blockIdx.y * items_cap;
-    small += (int64_t)blockIdx.y * 8;
-    offs += (int64_t)blockIdx.y * hist_ints;
-    const int c = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63;
-    const int nb = 1 << bits;
-    const int *k = skeys + p0;
-    auto lower = [&](int v) {
-        if (np == 0) return 0;
-        const int dh = v >> shift;
-        if (dh >= nb) return (int)np;
-        int lo = offs[(int64_t)dh * tiles];
-        int hi = dh + 1 < nb ? offs[(int64_t)(dh + 1) * tiles] : (int)np;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (k[mid] < v) lo = mid + 1;
-            else hi = mid;
+    for (int e = tid; e < 16 * nl; e += 1024) wcnt[e] = 0;
+    const Chunk c = find_chunk(blockIdx.x, nb, np, hist + (int64_t)nb * tiles, scr, &found);
+    if (c.b < 0) return;                // the same for every thread
+    const int na = min(c.cnt - c.j * kLocalTile, kLocalTile);
+    const int rounds = (na + 1023) >> 10;
+    const int64_t in0 = p0 + c.start + (int64_t)c.j * kLocalTile + wid * 64 * rounds;
+    const int left = na - wid * 64 * rounds;        // elements from this wave's first on
+    int key[RM], val[RM];
+    particle4<T> rec[RM];
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        const bool act = r < rounds && r * 64 + lane < left;
+        const int64_t i = act ? in0 + r * 64 + lane : p0;
+        key[r] = act ? keys_in[i] : -1;
+        val[r] = act ? vals_in[i] : 0;
+        rec[r] = act ? recs_in[i] : particle4<T>{T(0), T(0), T(0), T(0)};
+    }
+    // rank among the wave's earlier elements of the same digit (as k_rb_scatter)
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    int rank[RM];
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        rank[r] = 0;
+        if (r < rounds && r * 64 < left) {          // the same for the whole wave
+            const bool act = key[r] >= 0;
+            const int d = key[r] & (nl - 1);
+            const uint64_t peers = digit_peers(act, d, lbits);
+            const int before = __popcll(peers & lt);
+            const int base = act ? wcnt[wid * nl + d] : 0;
+            __builtin_amdgcn_wave_barrier();
+            rank[r] = base + before;
+            if (act && before == 0) wcnt[wid * nl + d] = base + __popcll(peers);
+            __builtin_amdgcn_wave_barrier();
         }
-        return lo;
-    };
-    const int s0 = lower(c < K ? c : K);
-    int s1 = __shfl_down(s0, 1, 64);
-    if (lane == 63 && c < K) s1 = lower(c + 1);
-    if (c <= K) start[c] = s0;
-    if (items != nullptr && c < K && s1 - s0 > dense_thr) {
-        const int J = (s1 - s0 + kDenseItem - 1) / kDenseItem;
-        const int base = atomicAdd(small, J);
-        const int ps = J > 1 ? atomicAdd(small + 3, J) : -1;
-        for (int j = 0; j < J; ++j)
-            if (base + j < items_cap - splits_cap) items[base + j] = int4{c, j, J, ps};
-        if (J > 1) {
-            const int si = atomicAdd(small + 4, 1);
-            if (si < splits_cap) items[items_cap - splits_cap + si] = int4{c, J, ps, 0};
+    }
+    __syncthreads();
+    // thread d (< nl <= 1024): prefix of its digit over the waves, the chunk's
+    // count and, for a bucket of several chunks, the others' counts
+    int tot = 0, all = 0, before = 0;
+    if (tid < nl) {
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int v = wcnt[w * nl + tid];
+            wcnt[w * nl + tid] = tot;
+            tot += v;
         }
+        all = tot;
+        if (c.J > 1) {
+            const int *h = hist + (int64_t)nb * (tiles + 1) + (int64_t)c.mbase * nl + tid;
+            all = 0;
+#pragma unroll 8
+            for (int j = 0; j < c.J; ++j) {
+                const int v = h[(int64_t)j * nl];
+                before += j < c.j ? v : 0;
+                all += v;
+            }
+        }
+    }
+    // exclusive scans over the digits: the chunk's counts and the bucket's
+    int inc = tot, ia = all;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(inc, off, 64), a = __shfl_up(ia, off, 64);
+        if (lane >= off) {
+            inc += u;
+            ia += a;
+        }
+    }
+    if (lane == 63) {                   // find_chunk's last barrier is behind
+        scr[wid] = inc;
+        scr[16 + wid] = ia;
+    }
+    __syncthreads();
+    if (tid < nl) {
+        int l = inc - tot, first = c.start + ia - all;
+        for (int w = 0; w < wid; ++w) {
+            l += scr[w];
+            first += scr[16 + w];
+        }
+        const int cell = (c.b << lbits) | tid;
+        if (c.j == 0 && cell < K) {
+            start[cell] = first;
+            if (items != nullptr && all > dense_thr)
+                list_dense(cell, all, whole, items + (int64_t)blockIdx.y * items_cap, items_cap,
+                           splits_cap, small + (int64_t)blockIdx.y * 8);
+        }
+        ls[tid] = l;
+        goff[tid] = first + before - l;
+    }
+    if (blockIdx.x == 0 && tid == 0) start[K] = (int)np;
+    __syncthreads();
+    int lidx[RM];
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        const int d = key[r] & (nl - 1);
+        lidx[r] = key[r] >= 0 ? ls[d] + wcnt[wid * nl + d] + rank[r] : 0;
+    }
+    __syncthreads();                    // the counts' region becomes the staging area
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+        if (key[r] >= 0) sint[lidx[r]] = key[r];
+    __syncthreads();
+    int dst[RM];
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        const int jj = r * 1024 + tid;
+        dst[r] = 0;
+        if (jj < na) {
+            const int k = sint[jj];
+            dst[r] = goff[k & (nl - 1)] + jj;
+            keys_out[p0 + dst[r]] = k;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+        if (key[r] >= 0) sint[lidx[r]] = val[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        const int jj = r * 1024 + tid;
+        if (jj < na) {
+            const int v = sint[jj];
+            vals_out[p0 + dst[r]] = v;
+            if (pos != nullptr) pos[v] = (int)(p0 + dst[r]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+        if (key[r] >= 0) srec[lidx[r]] = rec[r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < RM; ++r) {
+        const int jj = r * 1024 + tid;
+        if (jj < na) recs_out[p0 + dst[r]] = srec[jj];
     }
 }
 
-// Digit widths of the passes for keys below K (at most kRadixMaxBits each,
-// as even as possible).
-static int radix_passes(int K, int widths[8]) {
-    int bits = 0;
-    while ((1 << bits) < K) ++bits;
-    if (bits == 0) bits = 1;
-    const int np = (bits + kRadixMaxBits - 1) / kRadixMaxBits;
-    for (int i = 0; i < np; ++i) widths[i] = bits / np + (i < bits % np ? 1 : 0);
-    return np;
+// Few particles and cells: two launches in place of the sort's five or six.
+// k_bin_keys writes every particle's cell; in k_bin_small every block counts
+// the cells of ALL particles in LDS, those before its tile of kSmallTile
+// particles apart, scans the counts and places its own tile, whose four waves
+// rank one after the other.  A call this small is bound by launches and
+// latency, and reading 128 KB of cells from L2 once per block costs less than
+// the histogram, scan and second-pass launches it replaces.  (Cells recomputed
+// from the positions by every block: one launch, but 25 us at 32768 particles.)
+constexpr int kSmallTile = 256;
+template <typename T>
+__global__ void __launch_bounds__(256) k_bin_keys(
+    const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
+    const T *__restrict__ y, const T *__restrict__ z, T inv_h, int nc, int3 lim, int periodic,
+    int *__restrict__ keys, int *__restrict__ flag, int *__restrict__ small) {
+    int64_t p0, np;
+    sys_range(prange, n, p0, np);
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j == 0) reset_counts(small + (int64_t)blockIdx.y * 8);
+    if (j >= np) return;
+    int ix, iy, iz, out = 0;
+    T u;
+    cell_coord(x[p0 + j], inv_h, nc, lim.x, periodic, ix, u, out);
+    cell_coord(y[p0 + j], inv_h, nc, lim.y, periodic, iy, u, out);
+    cell_coord(z[p0 + j], inv_h, nc, lim.z, periodic, iz, u, out);
+    if (out) *flag = 1;
+    keys[p0 + j] = (iz * nc + iy) * nc + ix;
+}
+
+template <typename T>
+__global__ void __launch_bounds__(1024) k_bin_small(
+    const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
+    const T *__restrict__ y, const T *__restrict__ z, const T *__restrict__ q, T inv_h, int nc,
+    int periodic, int K, int bits, const int *__restrict__ keys, int *__restrict__ keys_out,
+    int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out, int *__restrict__ pos,
+    int *__restrict__ start, int dense_thr, int whole, int4 *__restrict__ items,
+    int64_t items_cap, int64_t splits_cap, int *__restrict__ small) {
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ int scr[16];
+    int64_t p0, np;
+    sys_range(prange, n, p0, np);
+    const int nb = 1 << bits, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int t0 = blockIdx.x * kSmallTile;
+    if (t0 >= np && blockIdx.x > 0) return;         // block 0 writes the starts
+    keys += p0;
+    int *cur = (int *)lds_raw, *rest = cur + nb;    // counts before the tile, and from it on
+    // this block's own records, in flight behind the counting
+    const int64_t i = p0 + t0 + tid;
+    const bool act = tid < kSmallTile && t0 + tid < np;
+    particle4<T> rec{T(0), T(0), T(0), T(0)};
+    int key = 0, slot = 0;
+    if (act) key = cell_record(x, y, z, q, i, inv_h, nc, periodic, rec);
+    for (int d = tid; d < 2 * nb; d += 1024) cur[d] = 0;
+    __syncthreads();
+    constexpr int U = 8;
+    for (int base = tid; base < np; base += 1024 * U) {
+        int kv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) kv[u] = keys[base + u * 1024 < np ? base + u * 1024 : 0];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = base + u * 1024;
+            if (j < np) atomicAdd(&(j < t0 ? cur : rest)[kv[u]], 1);
+        }
+    }
+    __syncthreads();
+    // thread tid scans the cells [tid C, tid C + C)
+    constexpr int C = kSmallMaxK / 1024;
+    int tot[C], sum = 0;
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+        const int d = tid * C + u;
+        tot[u] = d < nb ? cur[d] + rest[d] : 0;
+        sum += tot[u];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int u = __shfl_up(inc, off, 64);
+        if (lane >= off) inc += u;
+    }
+    if (lane == 63) scr[wid] = inc;
+    __syncthreads();
+    int first = inc - sum;
+    for (int w = 0; w < wid; ++w) first += scr[w];
+    start += (int64_t)blockIdx.y * (K + 1);
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+        const int d = tid * C + u;
+        if (d < nb) {
+            cur[d] += first;
+            if (blockIdx.x == 0 && d < K) {
+                start[d] = first;
+                if (items != nullptr && tot[u] > dense_thr)
+                    list_dense(d, tot[u], whole, items + (int64_t)blockIdx.y * items_cap, items_cap,
+                               splits_cap, small + (int64_t)blockIdx.y * 8);
+            }
+        }
+        first += tot[u];
+    }
+    if (blockIdx.x == 0 && tid == 0) start[K] = (int)np;
+    // place the tile
+    const uint64_t peers = digit_peers(act, key, bits);
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+    const int rank = __popcll(peers & lt);
+    for (int w = 0; w < kSmallTile / 64; ++w) {
+        __syncthreads();
+        if (wid == w && act) {
+            slot = cur[key] + rank;
+            __builtin_amdgcn_wave_barrier();
+            if (rank == 0) cur[key] = slot + __popcll(peers);
+        }
+    }
+    if (act) {
+        const int64_t o = p0 + slot;
+        keys_out[o] = key;
+        vals_out[o] = (int)i;
+        recs_out[o] = rec;
+        if (pos != nullptr) pos[i] = (int)o;
+    }
 }
 
 template <typename T, int R>
@@ -474,54 +851,47 @@ static hipError_t radix_bin(const BinArgs &a, int K, int64_t maxn, hipStream_t s
     const T inv_h = T(a.inv_h);
     const int nsys = a.nsys > 0 ? a.nsys : 1;
     const int tiles = (int)bin_tiles(maxn);
-    const int64_t hist_ints = bin_hist_ints(maxn);
-    int widths[8];
-    const int passes = radix_passes(K, widths);
-    int *kA = a.cell_of, *vA = a.slot, *kF = a.scell, *vF = a.perm;
-    particle4<T> *rA = (particle4<T> *)a.recs, *rF = (particle4<T> *)a.sorted;
-    const int *kin = nullptr, *vin = nullptr;
-    const particle4<T> *rin = nullptr;
-    int shift = 0;
+    const int64_t hist_ints = bin_hist_ints(maxn, K);
+    const int hb = bin_high_bits(maxn, K), lb = bin_key_bits(K) - hb, nb = 1 << hb;
     const int3 lim = make_int3(a.lim[0] > 0 ? a.lim[0] : a.ncell, a.lim[1] > 0 ? a.lim[1] : a.ncell,
                                a.lim[2] > 0 ? a.lim[2] : a.ncell);
-    for (int ps = 0; ps < passes; ++ps) {
-        const int bits = widths[ps], first = ps == 0, last = ps == passes - 1;
-        // alternate so that the last pass lands in (scell, perm, sorted)
-        const bool to_final = ((passes - 1 - ps) & 1) == 0;
-        int *ko = to_final ? kF : kA, *vo = to_final ? vF : vA;
-        particle4<T> *ro = to_final ? rF : rA;
-        hipLaunchKernelGGL((k_rb_hist<T, R>), dim3(tiles, nsys), dim3(1024), 0, s, a.prange, a.n,
-                           first, (const T *)a.x, (const T *)a.y, (const T *)a.z, inv_h, a.ncell,
-                           lim, a.periodic, kin, a.count, hist_ints, tiles, shift, bits, a.flag,
-                           a.small);
-        const int64_t L = (int64_t)(1 << bits) * tiles;
-        if (L <= kScanOneBlock) {
-            hipLaunchKernelGGL(k_rb_scan1, dim3(1, nsys), dim3(1024), 0, s, L, hist_ints, a.count);
-        } else {
-            const int st = (int)((L + 4095) / 4096);
-            hipLaunchKernelGGL(k_rb_scan_sums, dim3(st, nsys), dim3(1024), 0, s, L, hist_ints,
-                               a.count, a.tile_sums);
-            hipLaunchKernelGGL(k_rb_scan, dim3(st, nsys), dim3(1024), 0, s, L, hist_ints,
-                               a.count, a.tile_sums);
-        }
-        const size_t lds = scatter_lds<T, R>(bits);
-        if (lds > 65536) {
-            const hipError_t e = set_max_lds((const void *)k_rb_scatter<T, R>, lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL((k_rb_scatter<T, R>), dim3(tiles, nsys), dim3(1024), lds, s, a.prange,
-                           a.n, first, last, (const T *)a.x, (const T *)a.y, (const T *)a.z,
-                           (const T *)a.q, inv_h, a.ncell, a.periodic, kin, vin, rin, ko, vo, ro,
-                           a.pos, a.count, hist_ints, tiles, shift, bits);
-        kin = ko;
-        vin = vo;
-        rin = ro;
-        if (!last) shift += bits;
+    particle4<T> *recs = (particle4<T> *)a.recs;
+    hipLaunchKernelGGL((k_rb_hist<T, R>), dim3(tiles, nsys), dim3(1024), 0, s, a.prange, a.n,
+                       (const T *)a.x, (const T *)a.y, (const T *)a.z, inv_h, a.ncell, lim,
+                       a.periodic, a.count, hist_ints, tiles, lb, hb, a.flag, a.small);
+    const int64_t L = (int64_t)nb * tiles;
+    if (L <= kScanOneBlock) {
+        hipLaunchKernelGGL(k_rb_scan1, dim3(1, nsys), dim3(1024), 0, s, L, hist_ints, tiles, a.count);
+    } else {
+        const int st = (int)((L + 4095) / 4096);
+        hipLaunchKernelGGL(k_rb_scan_sums, dim3(st, nsys), dim3(1024), 0, s, L, hist_ints, a.count,
+                           a.tile_sums);
+        hipLaunchKernelGGL(k_rb_scan, dim3(st, nsys), dim3(1024), 0, s, L, hist_ints, tiles, a.count,
+                           a.tile_sums);
     }
-    hipLaunchKernelGGL(k_rb_bounds, dim3((K + 1 + 255) / 256, nsys), dim3(256), 0, s, a.prange,
-                       a.n, K, a.scell, a.start, a.dense_threshold, a.items, a.items_cap,
-                       dense_splits_cap_of(a.slots_cap), a.small, a.count, hist_ints, tiles, shift,
-                       widths[passes - 1]);
+    size_t lds = scatter_lds<T, R>(hb);
+    hipError_t e;
+    if (lds > 65536 && (e = set_max_lds((const void *)k_rb_scatter<T, R>, lds)) != hipSuccess)
+        return e;
+    const bool one = lb == 0;           // the buckets are the cells
+    hipLaunchKernelGGL((k_rb_scatter<T, R>), dim3(tiles, nsys), dim3(1024), lds, s, a.prange, a.n,
+                       (const T *)a.x, (const T *)a.y, (const T *)a.z, (const T *)a.q, inv_h,
+                       a.ncell, a.periodic, one ? a.scell : a.cell_of, one ? a.perm : a.slot,
+                       one ? (particle4<T> *)a.sorted : recs, a.count, hist_ints, tiles, lb, hb, K,
+                       one ? a.pos : nullptr, one ? a.start : nullptr, a.dense_threshold, a.whole,
+                       a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
+    if (one) return hipGetLastError();
+    // every bucket makes a chunk, and every kLocalTile particles at most one more
+    const unsigned chunks = (unsigned)(nb + maxn / kLocalTile);
+    if (maxn > kLocalTile)
+        hipLaunchKernelGGL(k_rb_hist2, dim3(chunks, nsys), dim3(1024), 0, s, a.prange, a.n,
+                           a.cell_of, a.count, hist_ints, tiles, nb, lb);
+    lds = local_lds<T>(lb);
+    if ((e = set_max_lds((const void *)k_rb_local<T>, lds)) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_rb_local<T>, dim3(chunks, nsys), dim3(1024), lds, s, a.prange, a.n, K,
+                       a.cell_of, a.slot, recs, a.scell, a.perm, (particle4<T> *)a.sorted, a.pos,
+                       a.start, a.count, hist_ints, tiles, nb, lb, a.dense_threshold, a.whole,
+                       a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
     return hipGetLastError();
 }
 
@@ -529,14 +899,28 @@ template <typename T>
 hipError_t launch_bin(const BinArgs &a, hipStream_t s) {
     const int K = a.ncell * a.ncell * a.ncell;
     const int64_t maxn = a.prange ? a.max_np : a.n;
+    const int nsys = a.nsys > 0 ? a.nsys : 1;
     if (maxn == 0) {
-        // every system is empty: zero starts, and the item counts reset here
-        const int nsys = a.nsys > 0 ? a.nsys : 1;
-        hipLaunchKernelGGL(k_rb_reset_items, dim3(1), dim3(64), 0, s, nsys, a.small);
-        hipLaunchKernelGGL(k_rb_bounds, dim3((K + 1 + 255) / 256, nsys), dim3(256), 0, s,
-                           a.prange, a.n, K, a.scell, a.start, a.dense_threshold, a.items,
-                           a.items_cap, dense_splits_cap_of(a.slots_cap), a.small, a.count,
-                           (int64_t)0, 1, 0, 1);
+        hipLaunchKernelGGL(k_bin_empty, dim3((K + 1 + 255) / 256, nsys), dim3(256), 0, s, K,
+                           a.start, a.small);
+        return hipGetLastError();
+    }
+    if (bin_is_small(maxn, K, nsys)) {
+        const int bits = bin_key_bits(K);
+        const unsigned blocks = (unsigned)((maxn + 255) / 256);
+        const int3 lim =
+            make_int3(a.lim[0] > 0 ? a.lim[0] : a.ncell, a.lim[1] > 0 ? a.lim[1] : a.ncell,
+                      a.lim[2] > 0 ? a.lim[2] : a.ncell);
+        static_assert(kSmallTile == 256, "one grid for both kernels");
+        hipLaunchKernelGGL(k_bin_keys<T>, dim3(blocks, nsys), dim3(256), 0, s, a.prange, a.n,
+                           (const T *)a.x, (const T *)a.y, (const T *)a.z, T(a.inv_h), a.ncell, lim,
+                           a.periodic, a.cell_of, a.flag, a.small);
+        hipLaunchKernelGGL(k_bin_small<T>, dim3(blocks, nsys), dim3(1024),
+                           (size_t)2 * sizeof(int) << bits, s, a.prange, a.n, (const T *)a.x,
+                           (const T *)a.y, (const T *)a.z, (const T *)a.q, T(a.inv_h), a.ncell,
+                           a.periodic, K, bits, a.cell_of, a.scell, a.perm,
+                           (particle4<T> *)a.sorted, a.pos, a.start, a.dense_threshold, a.whole,
+                           a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
         return hipGetLastError();
     }
     switch (bin_tile_items(maxn)) {

@@ -578,24 +578,26 @@ struct BinArgs {
     // be a corner of the ncell^3 mesh; a particle beyond it sets flag
     // (0: ncell)
     int lim[3] = {0, 0, 0};
-    // [n] key/value/record ping-pong arrays of the radix sort; the sorted
-    // cell, the permutation (caller index of every sorted slot) and the
-    // sorted records end in scell, perm, sorted
+    // [n] keys, caller indices (and recs) of the partition; the sorted cell,
+    // the permutation (caller index of every sorted slot) and the sorted
+    // records end in scell, perm, sorted
     int *cell_of, *slot, *scell, *perm;
-    void *recs;        // particle4<T>[n] records between passes
+    void *recs;        // particle4<T>[n] records of the partition
     int *start;        // [nsys][K + 1] first sorted slot of every cell (system-relative)
     int *flag;         // set when an open-boundary particle lies outside the box
     // [nsys][items_cap] dense-cell items {cell, chunk, chunks, first partial
-    // slot or -1} followed by the split cells (or null: none built);
-    // small[8 s + 0] counts the items, small[8 s + 3] the partial slots and
-    // small[8 s + 4] the split cells of system s
+    // slot or -1} followed by the split cells (or null: none built); whole:
+    // one item per dense cell, none split
+    int whole;
     int4 *items;
     int64_t items_cap, slots_cap;
-    int *small;
-    int *count;        // [nsys][bin_hist_ints(max_np)] radix histograms / offsets
-    int *tile_sums;    // [nsys][bin_scan_tiles(max_np)] scan scratch
-    int *pos;          // [n] sorted slot of each particle in the caller's order (or null)
     int dense_threshold;
+    // [nsys][8] counts, zeroed here: [0] items, [3] partial slots, [4] split
+    // cells, [5..7] near-field lists
+    int *small;
+    int *count;        // [nsys][bin_hist_ints(max_np, K)] histograms / offsets
+    int *tile_sums;    // [nsys][bin_scan_tiles(max_np, K)] scan scratch
+    int *pos;          // [n] sorted slot of each particle in the caller's order (or null)
     void *sorted;      // particle4<T>[n]
     // batch of nsys systems on this mesh (prange null: one system of n)
     const int64_t *prange;
@@ -604,9 +606,8 @@ struct BinArgs {
 };
 template <typename T>
 hipError_t launch_bin(const BinArgs &a, hipStream_t s);
-// Radix-sort tiles: 1024 R elements, R = 1, 2 or 4 growing with the
-// particle count, and at most 2^9 buckets per digit.
-constexpr int kRadixMaxBits = 9;
+// Partition tiles: 1024 R elements, R = 1, 2 or 4 growing with the particle
+// count.
 constexpr int bin_tile_items(int64_t max_np) {
     return max_np >= (int64_t(1) << 21) ? 4 : (max_np >= (int64_t(1) << 20) ? 2 : 1);
 }
@@ -617,15 +618,53 @@ constexpr int64_t bin_tiles(int64_t max_np) {
 }
 constexpr int64_t bin_max64(int64_t a, int64_t b) { return a > b ? a : b; }
 constexpr int64_t bin_min64(int64_t a, int64_t b) { return a < b ? a : b; }
-// Histogram ints per system for every particle count up to max_np (the tile
-// count is not monotonic where R steps up, hence the maximum).
-constexpr int64_t bin_hist_ints(int64_t max_np) {
-    return (int64_t(1) << kRadixMaxBits) *
-           bin_max64(bin_tiles(max_np),
-                     bin_max64(bin_tiles(bin_min64(max_np, (int64_t(1) << 21) - 1)),
-                               bin_tiles(bin_min64(max_np, (int64_t(1) << 20) - 1))));
+// Bits of the cell index, and those that the partition takes.  A bucket is
+// sorted by one block up to kLocalTile particles, so the partition takes the
+// bits that bring a uniform bucket to half of that -- all of them up to 512
+// cells; at most 9 (beyond, the
+// runs that a tile of the partition writes get shorter than a cache line) and
+// what the local sort leaves, which takes 10 (above 2^20 cells the partition
+// takes 11, the most that fit LDS).
+constexpr int kRadixMaxBits = 11, kLocalMaxBits = 10;
+constexpr int kLocalTile = 4096;
+constexpr int bin_key_bits(int64_t K) {
+    int b = 1;
+    while ((int64_t(1) << b) < K) ++b;
+    return b;
 }
-constexpr int64_t bin_scan_tiles(int64_t max_np) { return (bin_hist_ints(max_np) + 4095) / 4096; }
+constexpr int bin_high_bits(int64_t max_np, int64_t K) {
+    const int bits = bin_key_bits(K);
+    if (bits <= 9) return bits;         // the partition is the whole sort
+    int hb = 1;
+    while (hb < 9 && hb < bits && (max_np >> hb) > kLocalTile / 2) ++hb;
+    const int least = bits > 20 ? kRadixMaxBits : bits - kLocalMaxBits;
+    return hb > least ? hb : least;
+}
+// Histogram ints per system for every particle count up to max_np (the tile
+// count is not monotonic where R steps up, hence the maximum): the partition's
+// [buckets][tiles] and the bucket starts, then the low-bit histograms of the
+// chunks of large buckets (one of c > kLocalTile particles makes less than
+// 2 c / kLocalTile).
+constexpr int64_t bin_hist_ints(int64_t max_np, int64_t K) {
+    const int bits = bin_key_bits(K);
+    const int hb = bits > 19 ? kRadixMaxBits : (bits < 9 ? bits : 9);
+    const int64_t tiles = bin_max64(bin_tiles(max_np),
+                                    bin_max64(bin_tiles(bin_min64(max_np, (int64_t(1) << 21) - 1)),
+                                              bin_tiles(bin_min64(max_np, (int64_t(1) << 20) - 1))));
+    return (((tiles + 1) << hb) + ((2 * max_np / kLocalTile + 1) << kLocalMaxBits) + 63) / 64 * 64;
+}
+constexpr int64_t bin_scan_tiles(int64_t max_np, int64_t K) {
+    return (bin_hist_ints(max_np, K) + 4095) / 4096;
+}
+// The two-launch binning, whose blocks each count all particles of a system:
+// at most kSmallMaxN particles on kSmallMaxK cells, and for a batch no more
+// counting in all than one such system has.
+constexpr int64_t kSmallMaxN = 32768;
+constexpr int kSmallMaxK = 4096;
+constexpr bool bin_is_small(int64_t max_np, int64_t K, int nsys) {
+    return max_np > 0 && max_np <= kSmallMaxN && K <= kSmallMaxK &&
+           nsys * max_np <= kSmallMaxN * kSmallMaxN / max_np;
+}
 
 // Dense cells (above the P2M threshold, never below kDenseMinThreshold) are
 // cut into items of kDenseItem sorted particles, one wave each; a cell of J
@@ -652,6 +691,7 @@ struct P2MArgs {
     const int *start;
     int dense_threshold;            // cells above it are reduced as dense items
     const int4 *items;              // dense items of the binning (see BinArgs)
+    int whole;                      // they are whole cells
     int64_t items_cap;
     const int *small;
     float *partial;                 // [nsys][slots_cap][P + 1] sums of the items of split cells

@@ -3,9 +3,10 @@
 //              per-cell sum q |r_rel|^2 used by the periodic correction.
 //              Light cells: a group of G lanes strides over the cell's sorted
 //              particles and reduces with cross-lane shuffles.  Dense cells
-//              (more than the dense threshold): extra workgroups of the same
-//              launch, one per cell, with FP64 accumulation and a fixed-order
-//              block reduction.
+//              (more than the dense threshold) are work items listed by the
+//              binning, taken by extra blocks of the same launch: one wave per
+//              kDenseItem particles, the items of a cell added by
+//              k_p2m_combine, or with few particles one block per cell
 //   k_l2p      eq. L2P for Phi; eq. L2L to destination order one and
 //              eq. phigrad for grad Phi; the per-particle terms of a charged
 //              periodic system (App. B, correction procedure; the uniform
@@ -40,21 +41,108 @@ __device__ __forceinline__ void wave_rs_step(A *v, int lane) {
     }
 }
 
-// Light cells (at most dense_thr particles): a group of G lanes per cell
-// strides over its sorted particles and reduces with cross-lane shuffles.
-template <int PO, typename T, int G>
-__global__ void __launch_bounds__(256) k_p2m(int K, const int *__restrict__ start,
+// Sum of one dense item by a wave: the sorted particles [s0, s1), at most
+// kDenseItem (eight per lane, their loads in flight together), then the
+// scattered wave sum per group of 64 components -- lane L ends with component
+// 64 g + L in acc[64 g].
+template <int PO, typename T>
+__device__ __forceinline__ void dense_item(const particle4<T> *__restrict__ sorted, int s0, int s1,
+                                           int lane, T *acc) {
+    constexpr int P = nreal(PO), NG = (P + 1 + 63) / 64, U = kDenseItem / 64;
+    particle4<T> r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int s = s0 + u * 64 + lane;
+        r[u] = sorted[s < s1 ? s : s1 - 1];
+    }
+#pragma unroll
+    for (int c = 0; c < NG * 64; ++c) acc[c] = T(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const T q = s0 + u * 64 + lane < s1 ? r[u].q : T(0);
+        accumulate_regular<PO, T>(-r[u].ux, -r[u].uy, -r[u].uz, q, acc);
+        acc[P] += q * (r[u].ux * r[u].ux + r[u].uy * r[u].uy + r[u].uz * r[u].uz);
+        __builtin_amdgcn_sched_barrier(0);   // one particle's terms at a time: 124 VGPRs, not 214
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) wave_rs_step<32, T>(acc + 64 * g, lane);
+}
+
+// Blocks [0, nlight): light cells (at most dense_thr particles), a group of G
+// lanes per cell.  The other blocks: the dense items of the binning.  WHOLE: an
+// item is a cell, its four waves take kDenseItem particles at a time and their
+// sums are added in FP64, in order within a wave, then over the waves.  Else an
+// item is kDenseItem particles of a cell and one wave's work; its sum is the
+// cell's moments (a cell of one item) or one of the partial sums that
+// k_p2m_combine adds.  Both kinds of block run side by side: in a launch of
+// their own the items took 29 us after the 33 us of the light cells on 2^22
+// clustered particles, and an empty launch 4 us of a call without dense cells.
+template <int PO, typename T, int G, bool WHOLE>
+__global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__restrict__ start,
                                              const particle4<T> *__restrict__ sorted,
-                                             int dense_thr, T *__restrict__ M,
-                                             const int64_t *__restrict__ prange) {
+                                             int dense_thr, const int4 *__restrict__ items,
+                                             int64_t items_cap, const int *__restrict__ small,
+                                             float *__restrict__ partial, int64_t slots_cap,
+                                             T *__restrict__ M, const int64_t *__restrict__ prange) {
     constexpr int P = nreal(PO);
     constexpr int NV = P + 1;
+    constexpr int NG = (NV + 63) / 64;
     {
         // system blockIdx.y of a batch: its cell arrays and sorted particles
         const int64_t sy = blockIdx.y;
         start += sy * (K + 1);
+        items += sy * items_cap;
+        small += sy * 8;
+        partial += sy * slots_cap * NV;
         M += sy * NV * K;
         if (prange != nullptr) sorted += prange[2 * sy];
+    }
+    if ((int)blockIdx.x >= nlight) {
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        const int nitems = small[0] < items_cap ? small[0] : (int)items_cap;
+        const int first = blockIdx.x - nlight, blocks = gridDim.x - nlight;
+        if constexpr (WHOLE) {
+            __shared__ double red[4][NV];
+            for (int it = first; it < nitems; it += blocks) {
+                const int cell = items[it].x, d0 = start[cell], d1 = start[cell + 1];
+                double sum[NG];
+#pragma unroll
+                for (int g = 0; g < NG; ++g) sum[g] = 0.0;
+                for (int i0 = d0 + wid * kDenseItem; i0 < d1; i0 += 4 * kDenseItem) {
+                    T acc[NG * 64];
+                    dense_item<PO, T>(sorted, i0, i0 + kDenseItem < d1 ? i0 + kDenseItem : d1, lane,
+                                      acc);
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) sum[g] += (double)acc[64 * g];
+                }
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    if (64 * g + lane < NV) red[wid][64 * g + lane] = sum[g];
+                __syncthreads();
+                for (int c = threadIdx.x; c < NV; c += 256)
+                    M[(int64_t)c * K + cell] = T((red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
+                __syncthreads();
+            }
+        } else {
+            for (int it = first * 4 + wid; it < nitems; it += blocks * 4) {
+                const int4 e = items[it];
+                const int cell = e.x, j = e.y, J = e.z, ps = e.w;
+                const int s0 = start[cell] + j * kDenseItem, s1e = start[cell + 1];
+                T acc[NG * 64];
+                dense_item<PO, T>(sorted, s0, s0 + kDenseItem < s1e ? s0 + kDenseItem : s1e, lane,
+                                  acc);
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    const int c = 64 * g + lane;
+                    if (c < NV) {
+                        if (J == 1) M[(int64_t)c * K + cell] = acc[64 * g];
+                        else if (ps + j < slots_cap)
+                            partial[(int64_t)(ps + j) * NV + c] = (float)acc[64 * g];
+                    }
+                }
+            }
+        }
+        return;
     }
     const int gid = blockIdx.x * 256 + threadIdx.x;
     const int cell = gid / G;
@@ -92,68 +180,6 @@ __global__ void __launch_bounds__(256) k_p2m(int K, const int *__restrict__ star
 #pragma unroll
         for (int c = 0; c < NV; ++c)
             if ((c & (G - 1)) == lane) M[(int64_t)c * K + cell] = acc[c];
-    }
-}
-
-// Dense items of the binning, one wave each: the item's kDenseItem sorted
-// particles (eight per lane), a scattered wave sum per group of 64
-// components, then the moments written directly (a cell of one item) or as
-// the cell's partial sum of this item (added by k_p2m_combine in FP64).
-template <int PO, typename T>
-__global__ void __launch_bounds__(256) k_p2m_dense(int K, const int *__restrict__ start,
-                                                   const particle4<T> *__restrict__ sorted,
-                                                   const int4 *__restrict__ items,
-                                                   int64_t items_cap,
-                                                   const int *__restrict__ small,
-                                                   float *__restrict__ partial,
-                                                   int64_t slots_cap, T *__restrict__ M,
-                                                   const int64_t *__restrict__ prange) {
-    constexpr int P = nreal(PO);
-    constexpr int NV = P + 1;
-    constexpr int NG = (NV + 63) / 64;
-    {
-        const int64_t sy = blockIdx.y;
-        start += sy * (K + 1);
-        items += sy * items_cap;
-        small += sy * 8;
-        partial += sy * slots_cap * NV;
-        M += sy * NV * K;
-        if (prange != nullptr) sorted += prange[2 * sy];
-    }
-    const int lane = threadIdx.x & 63;
-    const int nitems = small[0] < items_cap ? small[0] : (int)items_cap;
-    const int nwaves = gridDim.x * 4;
-    for (int it = blockIdx.x * 4 + (threadIdx.x >> 6); it < nitems; it += nwaves) {
-        const int4 e = items[it];
-        const int cell = e.x, j = e.y, J = e.z, ps = e.w;
-        const int s0 = start[cell] + j * kDenseItem;
-        const int s1e = start[cell + 1];
-        const int s1 = s0 + kDenseItem < s1e ? s0 + kDenseItem : s1e;
-        constexpr int U = kDenseItem / 64;
-        particle4<T> r[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int s = s0 + u * 64 + lane;
-            r[u] = sorted[s < s1 ? s : s1 - 1];
-        }
-        T acc[NG * 64];
-#pragma unroll
-        for (int c = 0; c < NG * 64; ++c) acc[c] = T(0);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const T q = s0 + u * 64 + lane < s1 ? r[u].q : T(0);
-            accumulate_regular<PO, T>(-r[u].ux, -r[u].uy, -r[u].uz, q, acc);
-            acc[P] += q * (r[u].ux * r[u].ux + r[u].uy * r[u].uy + r[u].uz * r[u].uz);
-        }
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            wave_rs_step<32, T>(acc + 64 * g, lane);
-            const int c = 64 * g + lane;
-            if (c < NV) {
-                if (J == 1) M[(int64_t)c * K + cell] = acc[64 * g];
-                else if (ps + j < slots_cap) partial[(int64_t)(ps + j) * NV + c] = (float)acc[64 * g];
-            }
-        }
     }
 }
 
@@ -352,10 +378,19 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
     const int *st = a.start;
     const particle4<T> *so = (const particle4<T> *)a.sorted;
     T *M = (T *)a.M;
-#define PMMM_P2M_G(GG)                                                                     \
-    case GG:                                                                               \
-        hipLaunchKernelGGL((k_p2m<PO, T, GG>), dim3(nlight, nsys), dim3(256), 0, s, K, st, \
-                           so, a.dense_threshold, M, a.prange);                            \
+    // blocks for the dense items: a wave per item (or a block per cell) up to
+    // the capacity, at most 2048 (128) over all systems -- they loop
+    const int64_t most = a.whole ? a.items_cap : (a.items_cap + 3) / 4;
+    const int64_t share = (a.whole ? 128 : 2048) / nsys + 8;
+    const int dense = (int)(most < share ? most : share);
+#define PMMM_P2M_W(GG, W)                                                                        \
+    hipLaunchKernelGGL((k_p2m<PO, T, GG, W>), dim3(nlight + dense, nsys), dim3(256), 0, s, K,    \
+                       nlight, st, so, a.dense_threshold, a.items, a.items_cap, a.small,         \
+                       a.partial, a.slots_cap, M, a.prange)
+#define PMMM_P2M_G(GG)                                                                           \
+    case GG:                                                                                     \
+        if (a.whole) PMMM_P2M_W(GG, true);                                                       \
+        else PMMM_P2M_W(GG, false);                                                              \
         break;
     switch (G) {
         PMMM_P2M_G(4)
@@ -367,12 +402,8 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
             return hipErrorInvalidValue;
     }
 #undef PMMM_P2M_G
-    if (a.items != nullptr) {
-        // waves for the dense items: up to the capacity, at most 8192 (they loop)
-        const int64_t dwaves = a.items_cap < 8192 ? a.items_cap : 8192;
-        const int dblocks = (int)((dwaves + 3) / 4);
-        hipLaunchKernelGGL((k_p2m_dense<PO, T>), dim3(dblocks, nsys), dim3(256), 0, s, K, st, so,
-                           a.items, a.items_cap, a.small, a.partial, a.slots_cap, M, a.prange);
+#undef PMMM_P2M_W
+    if (!a.whole) {
         // one block per split cell, up to 2048 (they loop)
         const int64_t nsplit = dense_splits_cap_of(a.slots_cap);
         const int cblocks = (int)(nsplit < 2048 ? nsplit : 2048);

@@ -1,0 +1,68 @@
+"""GPU parity of the far field where the binning changes its way: around the
+largest call of the two-launch form, around the chunk of the local sort (a
+bucket of one, two and many chunks), with few particles on many cells, on
+cell counts that are no power of two, and with cells above the dense
+threshold reduced by a P2M block or as listed items -- against the oracle at
+the bounds of gpu_helpers.BOUNDS, and bitwise equal when called again."""
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_parity, gpu_far, oracle_cfg
+from oracle import pmmm as opm
+from paper_1409_5981_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _clustered(n, n_cells, boundary, share, seed, dtype, edge):
+    """`share` of the particles in one cell off the mesh's centre, the rest
+    uniform, in random order; masses."""
+    rng = np.random.default_rng(seed)
+    k = int(n * share)
+    pos = rng.random((n, 3)) * n_cells
+    pos[:k] = n_cells // 3 + rng.random((k, 3))
+    pos = (pos[rng.permutation(n)] * edge).astype(dtype)
+    top = dtype(n_cells * edge)
+    pos = np.where(pos >= top, np.nextafter(top, dtype(0)), pos)
+    q = (rng.random(n) / n).astype(dtype)
+    return inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, n_cells, 2,
+                              boundary, box=float(n_cells * edge))
+
+
+@pytest.mark.parametrize("n,n_cells,boundary,share,prec", [
+    (255, 8, "open", 0.6, "f32"), (256, 8, "periodic", 0.6, "f64"),
+    (257, 8, "periodic", 0.9, "f32"), (3000, 6, "periodic", 0.5, "f32"),
+    (32768, 16, "periodic", 0.5, "f32"), (32769, 16, "periodic", 0.5, "f32"),
+    (32769, 16, "open", 0.0, "f64"), (5000, 32, "open", 0.7, "f32"),
+    (40000, 8, "open", 0.95, "f32"), (40000, 8, "open", 0.0, "f64"),
+    (33000, 5, "periodic", 0.3, "f32"), (140000, 32, "periodic", 0.2, "f32"),
+    (1050000, 16, "open", 0.1, "f32"), (2100000, 32, "open", 0.05, "f32")])
+def test_binning_forms(n, n_cells, boundary, share, prec):
+    dt = np.float32 if prec == "f32" else np.float64
+    ps = _clustered(n, n_cells, boundary, share, 70 + n % 97, dt, 1.0 / 32)
+    res, plan = gpu_far(ps, precision=prec)
+    ref = opm.far_field(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps))
+    assert_parity(res, ref.phi, ref.grad, prec, f"binning {n} on {n_cells}^3 {boundary} {prec}")
+    again, _ = gpu_far(ps, precision=prec, plan=plan)
+    assert all(np.array_equal(res[k], again[k]) for k in res)
+
+
+def test_binning_batch_of_small_systems():
+    """A batch small enough for the two-launch binning, with an empty system
+    and dense cells; then the same batch with larger systems."""
+    import torch
+    from paper_1409_5981_amd._lib import Batch
+    for sizes in ([300, 0, 2500, 77], [300, 9000, 0, 20000]):
+        sets = [_clustered(n, 8, "periodic", 0.5, 80 + n, np.float32, 1.0 / 8) for n in sizes]
+        batch = Batch([dict(n=8, p=2, boundary="periodic") for _ in sizes])
+        off = np.concatenate([[0], np.cumsum(sizes)])
+        t = [torch.from_numpy(np.concatenate([getattr(s, a) for s in sets])).cuda() for a in "xyzq"]
+        out = batch.far(off, *t)
+        torch.cuda.synchronize()
+        for i, s in enumerate(sets):
+            if s.n == 0:
+                continue
+            got = [o[off[i]:off[i + 1]].double().cpu().numpy() for o in out]
+            ref = opm.far_field(s.pos, s.q.astype(np.float64), oracle_cfg(s))
+            assert_parity({"phi": got[0], "grad": np.stack(got[1:], 1)}, ref.phi, ref.grad, "f32",
+                          f"batch system of {s.n}")
