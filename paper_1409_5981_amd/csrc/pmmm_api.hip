@@ -59,6 +59,7 @@ struct Plan {
     // stage is the local M2L over hier_table (margin hier_D, refinement hier_r)
     bool no_transfer = false;
     const float *hier_table = nullptr;
+    const float *hier_mat = nullptr;
     int hier_r = 0, hier_D = 0;
     int64_t K, ncol, ngreen;  // ngreen: stored transfer-kernel values
     double box, h, inv_h, alpha, alpha_cell;
@@ -555,6 +556,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
             m.slots_cap = pb.slots_cap;
             m.sorted = pb.sorted;
             m.M = pl->M;
+            m.order = pl->hier_mat ? hier_moment_order(pl->n, pl->hier_r) : 0;
             PMMM_HIP(launch_p2m<T>(m, s));
         }
         FFTArgs f{};
@@ -584,6 +586,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
             h.M = (const float *)pl->M;
             h.L = (float *)pl->L;
             h.table = pl->hier_table;
+            h.mat = pl->hier_mat;
             PMMM_HIP(launch_hier_m2l_f32(h, s));
         } else {
             for (int st = 0; st < 3; ++st) {
@@ -1349,7 +1352,7 @@ static int batch_far(pmmm_batch_s *b, const int64_t *offsets, const float *x, co
 // ------------------------------------------------ two-level hierarchy
 struct pmmm_hier_s {
     pmmm_plan_s *coarse = nullptr, *fine = nullptr;
-    float *table = nullptr;
+    float *table = nullptr, *mat = nullptr;
 };
 
 static void hier_destroy(pmmm_hier_s *h) {
@@ -1357,6 +1360,7 @@ static void hier_destroy(pmmm_hier_s *h) {
     if (h->coarse) destroy(h->coarse);
     if (h->fine) destroy(h->fine);
     if (h->table) hipFree(h->table);
+    if (h->mat) hipFree(h->mat);
     delete h;
 }
 
@@ -1417,11 +1421,22 @@ int pmmm_hier_create(const pmmm_params *coarse, int refine, void *stream, pmmm_h
         const size_t bytes = sizeof(float) * (size_t)W * W * W * h->fine->Q;
         hipError_t e = hipMalloc(&h->table, bytes);
         if (e == hipSuccess) e = build_hier_table_f32(h->fine->p, c, D, h->table, s);
+        // without the matrices (their rule, or memory is short) the table serves
+        const int64_t nmat = hier_matrix_floats(h->fine->p, h->fine->n, refine, D);
+        if (e == hipSuccess && nmat > 0) {
+            if (hipMalloc(&h->mat, sizeof(float) * (size_t)nmat) == hipSuccess) {
+                e = build_hier_matrices_f32(h->fine->p, D, h->table, h->mat, s);
+            } else {
+                h->mat = nullptr;
+                (void)hipGetLastError();
+            }
+        }
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             rc = hip_fail(e, "hierarchy table");
         } else {
             h->fine->hier_table = h->table;
+            h->fine->hier_mat = h->mat;
             h->fine->hier_r = refine;
             h->fine->hier_D = D;
         }

@@ -54,14 +54,6 @@ __device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int lim, int per
     u = s - T(i) - T(0.5);
 }
 
-// Tile handled by block b of G: blocks are dealt to the 8 XCDs in turn, and
-// this mapping gives each XCD a contiguous range of tiles, so the runs that
-// neighbouring tiles write side by side meet in one L2.
-__device__ __forceinline__ int xcd_tile(int b, int G) {
-    const int q = G >> 3, r = G & 7, x = b & 7;
-    return x * q + (x < r ? x : r) + (b >> 3);
-}
-
 // LDS of the scatter: the per-wave counts [16][nb], later reused as the
 // staging area of one tile, then ls[nb], goff[nb], wtot[16].
 template <typename T, int R>

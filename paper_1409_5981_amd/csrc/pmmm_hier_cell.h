@@ -5,7 +5,9 @@
 // the real-matrix form of eq. realmatrix with the real values of S at the
 // displacement I - J (cell units), read from a table over the margin
 // |d_a| <= D = (c + 1) r - 1.  The sum is taken directly, cell pair by cell
-// pair (the paper's local FFT convolution computes the same sum).
+// pair (the paper's local FFT convolution computes the same sum).  Two forms:
+// k_hier_m2l on the matrix cores, and k_hier_m2l_cell with lanes per cell for
+// what hier_mat_floats leaves to it.
 #pragma once
 
 #include "pmmm_hier.h"
@@ -187,12 +189,258 @@ __global__ __launch_bounds__(kHierCellThreads) void k_hier_m2l_cell(
     });
 }
 
+// ---- matrix-core form ----
+//
+// Bound by the multiply-adds: 2 P^2 flops per pair of fine cells.  Target
+// cells with the same position o inside their coarse cells see the same
+// displacements: lane = coarse cell, and one source offset j (in fine cells
+// from the target's coarse cell) has one P x P matrix T(o - j) for the whole
+// wave.  v_mfma_f32_4x4x1 with its A operand broadcast from one of its 16
+// blocks is then four rows of one column of T times one moment of 64 cells, so
+// a register of 64 coefficients feeds 16 products and no row is padded beyond
+// a multiple of four; its rate is twice what the vector unit reaches with one
+// wave issuing, and it leaves that unit to the FP64 sums.  The matrices are
+// written once per hierarchy in that register order, and the moments are read
+// grouped by fine position (moment_place): 64 consecutive floats a load, where
+// the strided rows made the loads the bound (16^3 x 4^3 cells, p = 6: 64.6 ms,
+// grouped 28.1; the lane-per-cell form, whose lanes gather different table
+// rows, 47.8).
+//
+// A row group is RBG blocks of four rows, at most nine (72 registers of FP64
+// sums, 36 of FP32 sums); its columns go in NCH chunks of KC <= 8, a chunk's
+// coefficients are NV registers of (column, row block) pairs, and the loads of
+// a chunk are issued before the products of the one before.  Four waves per
+// SIMD: at three (wider chunks, 136 registers) 64^3 x 2^3 cells, p = 4 took
+// 5.85 ms, now 4.74, of which the products are 3.45 (lane per cell 8.19);
+// 16^3 x 2^3 cells 101 us (212).
+template <int PO>
+struct HierMat {
+    static constexpr int P = nreal(PO), RB = (P + 3) / 4;
+    static constexpr int NG = (RB + 8) / 9, RBG = (RB + NG - 1) / NG;
+    static constexpr int NCH = 2 * ((P + 15) / 16), KC = (P + NCH - 1) / NCH;
+    static constexpr int NV = (KC * RBG + 15) / 16;
+    static constexpr int WAVES = RBG <= 7 && PO <= 6 ? 4 : 3;   // per SIMD, without spills
+    static constexpr int GSTRIDE = NCH * NV * 64, STRIDE = NG * GSTRIDE;   // floats per group, matrix
+};
+
+// Entry (row, col) of eq. realmatrix's matrix from the table row of S.
+__device__ __forceinline__ float hier_entry(const float *g, int row, int col) {
+    auto order = [](int a) {
+        int l = 0;
+        while ((l + 1) * (l + 1) <= a) ++l;
+        return l;
+    };
+    auto sgn = [](int k) { return (k & 1) ? -1.0f : 1.0f; };
+    auto re = [&](int n, int k) {
+        if (k > n || -k > n) return 0.0f;
+        return k >= 0 ? g[n * (n + 1) + k] : sgn(k) * g[n * (n + 1) - k];
+    };
+    auto im = [&](int n, int k) {
+        if (k == 0 || k > n || -k > n) return 0.0f;
+        return k > 0 ? g[n * (n + 1) - k] : -sgn(k) * g[n * (n + 1) + k];
+    };
+    const int l = order(row), mm = row - l * (l + 1), m = abs(mm);
+    const int lam = order(col), uu = col - lam * (lam + 1), mu = abs(uu), nn = l + lam;
+    if (mu == 0) return mm >= 0 ? re(nn, -m) : im(nn, -m);
+    const float sg = sgn(mu);
+    if (mm >= 0)
+        return uu > 0 ? re(nn, -(m + mu)) + sg * re(nn, -(m - mu))
+                      : sg * im(nn, -(m - mu)) - im(nn, -(m + mu));
+    return uu > 0 ? im(nn, -(m + mu)) + sg * im(nn, -(m - mu))
+                  : re(nn, -(m + mu)) - sg * re(nn, -(m - mu));
+}
+
+// All matrices in register order: thread = one float of mat; the lanes of an
+// unused pair or row hold zero.
+template <int PO>
+__global__ __launch_bounds__(256) void k_hier_matrices(const float *__restrict__ table,
+                                                       float *__restrict__ mat, int64_t cnt) {
+    using H = HierMat<PO>;
+    constexpr int Q = nreal(2 * PO);
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= cnt * H::STRIDE) return;
+    const int64_t d = t / H::STRIDE;
+    const int e = (int)(t - d * H::STRIDE);
+    const int lane = e & 63, v = (e >> 6) % H::NV, ch = (e >> 6) / H::NV % H::NCH;
+    const int grp = e / H::GSTRIDE;
+    const int pair = v * 16 + (lane >> 2), kk = pair / H::RBG;
+    const int col = ch * H::KC + kk, row = (grp * H::RBG + pair % H::RBG) * 4 + (lane & 3);
+    mat[t] = kk < H::KC && col < H::P && row < H::P ? hier_entry(table + d * Q, row, col) : 0.0f;
+}
+
+typedef float hier_f4 __attribute__((ext_vector_type(4)));
+constexpr int kHierMaxSplit = 8;
+constexpr int64_t kHierMaxMatBytes = (int64_t)512 << 20;
+
+// One block: the 64 coarse cells of group blockIdx.x / r^3 at one position o
+// and one row group (blockIdx.y); its waves take the sources in turn and
+// their FP64 sums are added through LDS in wave order.
+template <int PO>
+__global__ __launch_bounds__(64 * kHierMaxSplit, HierMat<PO>::WAVES) void k_hier_m2l(
+    const float *__restrict__ M, float *__restrict__ L, const float *__restrict__ mat, int ln, int lr,
+    int cutoff, int D) {
+    using H = HierMat<PO>;
+    constexpr int P = H::P, RBG = H::RBG, KC = H::KC, NV = H::NV, NCH = H::NCH;
+    extern __shared__ double part[];   // [split][4][64]
+    const int nf = 1 << ln, r = 1 << lr, lc = ln - lr, nc = 1 << lc;
+    const int K = 1 << (3 * ln), r3 = 1 << (3 * lr), W = 2 * D + 1;
+    const int split = (int)(blockDim.x >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int item = xcd_tile(blockIdx.x, gridDim.x), o = item & (r3 - 1);
+    const int ox = o & (r - 1), oy = (o >> lr) & (r - 1), oz = o >> (2 * lr);
+    const int C = (item >> (3 * lr)) * 64 + lane;
+    const bool active = C < 1 << (3 * lc);
+    const int cx = C & (nc - 1), cy = (C >> lc) & (nc - 1), cz = C >> (2 * lc);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)M, 0, (int)((int64_t)P * K * sizeof(float)), 0x00027000);
+    const int span = (2 * cutoff + 1) * r;
+    const int grp = blockIdx.y;
+
+    // next source of this wave that some lane has: its matrix and the byte
+    // offset of the lane's source cell (out of range, which loads zero, where
+    // the cell is outside the mesh)
+    const int j0 = -cutoff * r, j1 = j0 + span;
+    int jx = j0 + wave - split, jy = j0, jz = j0;
+    const float *T = nullptr;
+    int voff = 0;
+    auto next = [&]() -> bool {
+        while (true) {
+            for (jx += split; jx >= j1; jx -= span)
+                if (++jy == j1) {
+                    jy = j0;
+                    ++jz;
+                }
+            if (jz >= j1) return false;
+            const int dx = ox - jx, dy = oy - jy, dz = oz - jz;
+            int cheb = abs(dx) > abs(dy) ? abs(dx) : abs(dy);
+            cheb = cheb > abs(dz) ? cheb : abs(dz);
+            if (cheb <= cutoff) continue;
+            const int x = cx + (jx >> lr), y = cy + (jy >> lr), z = cz + (jz >> lr);
+            const bool in = active && (unsigned)x < (unsigned)nc && (unsigned)y < (unsigned)nc &&
+                            (unsigned)z < (unsigned)nc;
+            if (__ballot(in) == 0) continue;
+            const int oj = ((((jz & (r - 1)) << lr) | (jy & (r - 1))) << lr) | (jx & (r - 1));
+            voff = in ? ((oj << (3 * lc)) + (((z << lc) + y) << lc) + x) * (int)sizeof(float)
+                      : (int)0x80000000;
+            T = mat + ((int64_t)((dz + D) * W + (dy + D)) * W + (dx + D)) * H::STRIDE +
+                grp * H::GSTRIDE;
+            return true;
+        }
+    };
+    float mv[2][KC], av[2][NV];
+    auto load = [&](auto ich, float (&m)[KC], float (&a)[NV]) {
+        constexpr int ch = decltype(ich)::value;
+        static_for<0, NV>([&](auto iv) {
+            constexpr int v = decltype(iv)::value;
+            a[v] = T[(ch * NV + v) * 64 + lane];
+        });
+        static_for<0, KC>([&](auto ik) {
+            constexpr int k = decltype(ik)::value;
+            if constexpr (ch * KC + k < P)
+                m[k] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                     rs, voff, (ch * KC + k) * K * (int)sizeof(float), 0));
+        });
+    };
+    double acc[4 * RBG];
+    static_for<0, 4 * RBG>([&](auto ia) { acc[decltype(ia)::value] = 0.0; });
+    bool more = next();
+    if (more) load(std::integral_constant<int, 0>{}, mv[0], av[0]);
+    while (more) {
+        hier_f4 s[RBG];
+        static_for<0, RBG>([&](auto ib) { s[decltype(ib)::value] = hier_f4{0.0f, 0.0f, 0.0f, 0.0f}; });
+        static_for<0, NCH>([&](auto ich) {
+            constexpr int ch = decltype(ich)::value;
+            if constexpr (ch + 1 < NCH) {
+                load(std::integral_constant<int, ch + 1>{}, mv[(ch + 1) & 1], av[(ch + 1) & 1]);
+            } else {
+                more = next();
+                if (more) load(std::integral_constant<int, 0>{}, mv[0], av[0]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<0, KC>([&](auto ik) {
+                constexpr int k = decltype(ik)::value;
+                if constexpr (ch * KC + k < P)
+                    static_for<0, RBG>([&](auto ib) {
+                        constexpr int b = decltype(ib)::value, pair = k * RBG + b;
+                        s[b] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[ch & 1][pair / 16], mv[ch & 1][k],
+                                                                  s[b], 4, pair % 16, 0);
+                    });
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_for<0, RBG>([&](auto ib) {
+            constexpr int b = decltype(ib)::value;
+            static_for<0, 4>([&](auto ii) {
+                constexpr int i = decltype(ii)::value;
+                acc[4 * b + i] += (double)s[b][i];
+            });
+        });
+    }
+    const int I = active ? (((cz * r + oz) * nf) + cy * r + oy) * nf + cx * r + ox : 0;
+    static_for<0, RBG>([&](auto ib) {
+        constexpr int b = decltype(ib)::value;
+        __syncthreads();
+        static_for<0, 4>([&](auto ii) {
+            constexpr int i = decltype(ii)::value;
+            part[(wave * 4 + i) * 64 + lane] = acc[4 * b + i];
+        });
+        __syncthreads();
+        for (int i = wave; i < 4; i += split) {
+            const int row = (grp * RBG + b) * 4 + i;
+            if (row >= P || !active) continue;
+            double t = part[i * 64 + lane];
+            for (int w = 1; w < split; ++w) t += part[(w * 4 + i) * 64 + lane];
+            L[(int64_t)row * K + I] = (float)t;
+        }
+    });
+}
+
 }  // namespace hier_detail
+
+// Floats of the matrices of W^3 displacements for a fine mesh nf^3 refined by
+// r; 0 where the lane-per-cell form serves instead:
+//  - matrices above kHierMaxMatBytes (r = 8, or r = 4 with c = 2 at high
+//    orders), which are not kept;
+//  - fewer than 64 coarse cells: lanes of every wave would idle (2^3 cells,
+//    r = 4, p = 4: 452 us against 185);
+//  - above order 4, fewer than 1024 waves: a wave's chain of products is then
+//    the longer one (20000 particles, 4^3 cells, r = 2, whole call: p = 8
+//    305 us against 274, p = 10 431 against 404; 8^3, p = 5 195 against 184;
+//    from 1024 waves on 8^3, p = 6 248 against 270, 16^3, p = 8 1271 against
+//    2522; at p = 4 the matrices win down to 4^3 cells, 109 against 121).
+template <int PO>
+int64_t hier_mat_floats(int nf, int r, int D) {
+    using H = hier_detail::HierMat<PO>;
+    const int64_t nc = nf / r, r3 = (int64_t)r * r * r, items = (nc * nc * nc + 63) / 64 * r3;
+    if (nc * nc * nc < 64) return 0;
+    if (PO > 4 && items * H::NG * hier_detail::kHierMaxSplit < 1024) return 0;
+    const int64_t W = 2 * D + 1, cnt = W * W * W * H::STRIDE;
+    return cnt * (int64_t)sizeof(float) <= hier_detail::kHierMaxMatBytes ? cnt : 0;
+}
+
+template <int PO>
+hipError_t hier_mat_build(int D, const float *table, float *mat, hipStream_t s) {
+    const int64_t W = 2 * D + 1, cnt = W * W * W, n = cnt * hier_detail::HierMat<PO>::STRIDE;
+    hipLaunchKernelGGL(hier_detail::k_hier_matrices<PO>, dim3((unsigned)((n + 255) / 256)), dim3(256),
+                       0, s, table, mat, cnt);
+    return hipGetLastError();
+}
 
 // Launch of the kernel for order PO (one compile unit per order).
 template <int PO>
 hipError_t hier_cell_launch(const HierArgs &a, hipStream_t s) {
     const int64_t K = (int64_t)a.nf * a.nf * a.nf;
+    if (a.mat) {
+        using H = hier_detail::HierMat<PO>;
+        const int64_t nc = a.nf / a.r, r3 = (int64_t)a.r * a.r * a.r, items = (nc * nc * nc + 63) / 64 * r3;
+        // waves per item that share its sources: four waves per SIMD over
+        // the chip (256 CUs x 4 SIMDs), at most eight
+        int split = 1;
+        while (split < hier_detail::kHierMaxSplit && items * H::NG * split < 4096) split <<= 1;
+        hipLaunchKernelGGL(hier_detail::k_hier_m2l<PO>, dim3((unsigned)items, H::NG), dim3(64 * split),
+                           sizeof(double) * 256 * split, s, a.M, a.L, a.mat, __builtin_ctz(a.nf), __builtin_ctz(a.r), a.cutoff, a.D);
+        return hipGetLastError();
+    }
     constexpr int NG = hier_detail::hier_ngroups(PO);
     // Lanes per cell and row group: enough waves for four per SIMD
     // (256 CUs x 4 SIMDs), at most 8.

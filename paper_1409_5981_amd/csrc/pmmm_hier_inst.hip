@@ -10,5 +10,7 @@
 namespace pmmm {
 
 template hipError_t hier_cell_launch<PMMM_HIER_ORDER>(const HierArgs &, hipStream_t);
+template int64_t hier_mat_floats<PMMM_HIER_ORDER>(int, int, int);
+template hipError_t hier_mat_build<PMMM_HIER_ORDER>(int, const float *, float *, hipStream_t);
 
 }  // namespace pmmm

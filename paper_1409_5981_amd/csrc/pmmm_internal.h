@@ -686,6 +686,28 @@ constexpr int64_t dense_items_cap(int64_t max_np, int64_t K) {
            dense_splits_cap(max_np);
 }
 
+// Tile handled by block b of G: blocks are dealt to the 8 XCDs in turn, and
+// this mapping gives each XCD a contiguous range of tiles, so the runs that
+// neighbouring tiles write side by side meet in one L2.
+__device__ __forceinline__ int xcd_tile(int b, int G) {
+    const int q = G >> 3, r = G & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
+}
+
+// Place of a cell's moments in a component's row of M: the cell number, or
+// (order != 0, the fine level of a hierarchy) grouped by the cell's position
+// inside its coarse cell, so that the cells at one position are consecutive
+// in coarse order.  order = log2(fine edge) | log2(refinement) << 8, a cube
+// of 2^(..) cells per edge.
+__host__ __device__ inline int moment_place(int cell, int order) {
+    if (order == 0) return cell;
+    const int ln = order & 255, lr = order >> 8, lc = ln - lr;
+    const int x = cell & ((1 << ln) - 1), y = (cell >> ln) & ((1 << ln) - 1), z = cell >> (2 * ln);
+    const int m = (1 << lr) - 1;
+    const int o = ((((z & m) << lr) | (y & m)) << lr) | (x & m);
+    return (((((o << lc) | (z >> lr)) << lc) | (y >> lr)) << lc) | (x >> lr);
+}
+
 struct P2MArgs {
     int p, ncell, group;            // lanes per cell in the light path
     const int *start;
@@ -698,6 +720,7 @@ struct P2MArgs {
     int64_t slots_cap;
     const void *sorted;
     void *M;                        // [P + 1][K]: moments, then sum q |u|^2
+    int order;                      // place of a cell in a row of M (moment_place)
     const int64_t *prange;          // batch (see BinArgs)
     int nsys;
 };

@@ -83,7 +83,8 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
                                              int dense_thr, const int4 *__restrict__ items,
                                              int64_t items_cap, const int *__restrict__ small,
                                              float *__restrict__ partial, int64_t slots_cap,
-                                             T *__restrict__ M, const int64_t *__restrict__ prange) {
+                                             T *__restrict__ M, int order,
+                                             const int64_t *__restrict__ prange) {
     constexpr int P = nreal(PO);
     constexpr int NV = P + 1;
     constexpr int NG = (NV + 63) / 64;
@@ -119,8 +120,9 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
                 for (int g = 0; g < NG; ++g)
                     if (64 * g + lane < NV) red[wid][64 * g + lane] = sum[g];
                 __syncthreads();
+                const int at = moment_place(cell, order);
                 for (int c = threadIdx.x; c < NV; c += 256)
-                    M[(int64_t)c * K + cell] = T((red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
+                    M[(int64_t)c * K + at] = T((red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
                 __syncthreads();
             }
         } else {
@@ -135,7 +137,7 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
                 for (int g = 0; g < NG; ++g) {
                     const int c = 64 * g + lane;
                     if (c < NV) {
-                        if (J == 1) M[(int64_t)c * K + cell] = acc[64 * g];
+                        if (J == 1) M[(int64_t)c * K + moment_place(cell, order)] = acc[64 * g];
                         else if (ps + j < slots_cap)
                             partial[(int64_t)(ps + j) * NV + c] = (float)acc[64 * g];
                     }
@@ -177,9 +179,10 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
         for (int c = 0; c < NV; ++c) acc[c] += __shfl_xor(acc[c], off, 64);
     }
     if (write) {
+        const int at = moment_place(cell, order);
 #pragma unroll
         for (int c = 0; c < NV; ++c)
-            if ((c & (G - 1)) == lane) M[(int64_t)c * K + cell] = acc[c];
+            if ((c & (G - 1)) == lane) M[(int64_t)c * K + at] = acc[c];
     }
 }
 
@@ -193,7 +196,8 @@ __global__ void __launch_bounds__(256) k_p2m_combine(int K, int NV, const int4 *
                                                      int64_t items_cap,
                                                      const int *__restrict__ small,
                                                      const float *__restrict__ partial,
-                                                     int64_t slots_cap, T *__restrict__ M) {
+                                                     int64_t slots_cap, T *__restrict__ M,
+                                                     int order) {
     __shared__ double red[4][nreal(PMMM_PMAX) + 1];
     const int64_t splits_cap = dense_splits_cap_of(slots_cap);
     {
@@ -227,8 +231,9 @@ __global__ void __launch_bounds__(256) k_p2m_combine(int K, int NV, const int4 *
                           ((acc[4] + acc[5]) + (acc[6] + acc[7]));
         }
         __syncthreads();
+        const int at = moment_place(cell, order);
         for (int c = threadIdx.x; c < NV; c += 256)
-            if (ok) M[(int64_t)c * K + cell] = T((red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
+            if (ok) M[(int64_t)c * K + at] = T((red[0][c] + red[1][c]) + (red[2][c] + red[3][c]));
         __syncthreads();
     }
 }
@@ -386,7 +391,7 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
 #define PMMM_P2M_W(GG, W)                                                                        \
     hipLaunchKernelGGL((k_p2m<PO, T, GG, W>), dim3(nlight + dense, nsys), dim3(256), 0, s, K,    \
                        nlight, st, so, a.dense_threshold, a.items, a.items_cap, a.small,         \
-                       a.partial, a.slots_cap, M, a.prange)
+                       a.partial, a.slots_cap, M, a.order, a.prange)
 #define PMMM_P2M_G(GG)                                                                           \
     case GG:                                                                                     \
         if (a.whole) PMMM_P2M_W(GG, true);                                                       \
@@ -409,7 +414,7 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
         const int cblocks = (int)(nsplit < 2048 ? nsplit : 2048);
         hipLaunchKernelGGL(k_p2m_combine<T>, dim3(cblocks, nsys), dim3(256),
                            0, s, K, nreal(PO) + 1, a.items, a.items_cap, a.small, a.partial,
-                           a.slots_cap, M);
+                           a.slots_cap, M, a.order);
     }
     return hipGetLastError();
 }

@@ -48,6 +48,21 @@ def test_hier_far_matches_oracle(n, p, r, c, N):
     assert_parity(res, ref_phi, ref_grad, "f32", f"hier n={n} r={r} c={c} p={p}")
 
 
+# The matrix-core form of the fine level (above order 4 it takes meshes of at
+# least 1024 waves): one and several row groups, rows and columns that end
+# inside a block of four and inside a chunk, 64 and 4096 coarse cells, fine
+# offsets up to 7.
+@pytest.mark.parametrize("n,p,r,c,N", [(4, 1, 2, 2, 1500), (4, 2, 4, 1, 2500), (8, 4, 2, 1, 2500),
+                                       (8, 6, 2, 1, 2500), (8, 10, 2, 1, 1500), (16, 5, 2, 1, 1500)])
+def test_hier_matrix_form_matches_oracle(n, p, r, c, N):
+    print(f"hier matrices coarse {n}^3 p={p} r={r} c={c} N={N}", flush=True)
+    pos, q = _set(N, 100 * n + p)
+    cfg = opm.Config(n=n, p=p, boundary="open", cutoff=c)
+    ref_phi, ref_grad = ohier.far_field(pos.astype(np.float64), q.astype(np.float64), cfg, r)
+    res = _run(n, p, r, c, pos, q)
+    assert_parity(res, ref_phi, ref_grad, "f32", f"hier matrices n={n} r={r} c={c} p={p}")
+
+
 def test_hier_total_matches_oracle_and_direct_sum():
     n, p, r, c = 4, 5, 2, 2
     pos, q = _set(5000, 7)
