@@ -52,6 +52,7 @@ constexpr int64_t kStagedL2PMinN = int64_t(1) << 18;
 struct Plan {
     pmmm_params prm;
     int n, nf, p, P, Q, open, prec, cutoff, images;
+    int nfz, nzs;             // z transform length and spectra planes (nf and n, or shorter)
     int lim[3];               // cells per axis of the caller's box (open: a corner of n^3)
     int generic;              // periodic n not a power of two: direct-DFT stages
     void *spec2 = nullptr;    // generic: M2L output spectra
@@ -226,6 +227,19 @@ static void derive(Plan *pl, const pmmm_params *prm) {
     pl->generic = !is_pow2(pl->n);
     pl->open = prm->boundary == PMMM_OPEN;
     pl->nf = pl->open ? 2 * pl->n : pl->n;
+    // A flat open box is transformed over the power of two that holds its own
+    // z extent: the column stage's transforms, products and transfer kernel and
+    // the spectra shrink with it (planes above the box are skipped in any
+    // case: plan_conv).  Calls before and after: 48 x 40 x 32 cells, p = 6,
+    // 2^21 particles (64 of 128 points) 798 -> 509 us; 36 x 24 x 20, p = 8
+    // 2231 -> 754; 10 x 8 x 6, p = 5 (nothing shorter, 2 planes fewer) 71 -> 45
+    // with its binning.
+    pl->nzs = pl->n;
+    if (pl->open) {
+        pl->nzs = pl->n < 8 ? pl->n : 8;
+        while (pl->nzs < prm->nz) pl->nzs *= 2;
+    }
+    pl->nfz = pl->open ? 2 * pl->nzs : pl->nf;
     pl->p = prm->p;
     pl->P = nreal(pl->p);
     pl->Q = nreal(2 * pl->p);
@@ -235,7 +249,7 @@ static void derive(Plan *pl, const pmmm_params *prm) {
     pl->K = (int64_t)pl->n * pl->n * pl->n;
     pl->ncol = (int64_t)pl->nf * (pl->nf / 2 + 1);
     {
-        const int64_t nh = pl->nf / 2 + 1, nhp = (nh + 3) & ~3;
+        const int64_t nh = pl->nf / 2 + 1, nhp = (pl->nfz / 2 + 1 + 3) & ~3;
         pl->ngreen = nh * nh * pl->Q * nhp;
     }
     // box: edge of the computed cube (the caller's, or its embedding)
@@ -251,10 +265,10 @@ static size_t plan_bytes(const Plan *pl) {
     const size_t t = pl->tsize, c = 2 * t;
     size_t b = 0;
     b += (size_t)pl->ngreen * t;                         // green
-    b += (size_t)(pl->generic ? pl->nf : pl->nf / 2) * c; // twiddles
+    b += (size_t)((pl->generic ? pl->nf : pl->nf / 2) + (pl->nfz != pl->nf ? pl->nfz / 2 : 0)) * c; // twiddles
     if (pl->generic) b += (size_t)pl->P * pl->n * pl->ncol * c;  // M2L output spectra
     b += (size_t)(pl->P + 1) * pl->K * t;                // M
-    b += (size_t)pl->P * pl->n * pl->ncol * c;           // spectra
+    b += (size_t)pl->P * pl->nzs * pl->ncol * c;         // spectra
     b += (size_t)pl->P * pl->K * t;                      // L
     b += ((size_t)pl->K + 1 + 8) * sizeof(int);                                   // starts, small
     b += 8 * sizeof(double) + (size_t)pl->n * sizeof(double);                     // sums, plane sums
@@ -359,8 +373,11 @@ static int make_twiddles(Plan *pl, hipStream_t s) {
     std::vector<cplx<T>> tw(cnt);
     for (int k = 0; k < cnt; ++k)
         tw[k] = {T(std::cos(2.0 * M_PI * k / nf)), T(-std::sin(2.0 * M_PI * k / nf))};
-    PMMM_HIP(hipMalloc(&pl->tw, sizeof(cplx<T>) * cnt));
-    PMMM_HIP(hipMemcpyAsync(pl->tw, tw.data(), sizeof(cplx<T>) * cnt, hipMemcpyHostToDevice, s));
+    if (pl->nfz != nf)           // a shorter z transform's behind them
+        for (int k = 0; k < pl->nfz / 2; ++k)
+            tw.push_back({T(std::cos(2.0 * M_PI * k / pl->nfz)), T(-std::sin(2.0 * M_PI * k / pl->nfz))});
+    PMMM_HIP(hipMalloc(&pl->tw, sizeof(cplx<T>) * tw.size()));
+    PMMM_HIP(hipMemcpyAsync(pl->tw, tw.data(), sizeof(cplx<T>) * tw.size(), hipMemcpyHostToDevice, s));
     return PMMM_OK;
 }
 
@@ -368,7 +385,7 @@ static int alloc_plan(Plan *pl, hipStream_t s) {
     const size_t t = pl->tsize, c = 2 * t;
     if (!pl->no_transfer) {
         PMMM_HIP(hipMalloc(&pl->green, (size_t)pl->ngreen * t));
-        PMMM_HIP(hipMalloc(&pl->spec, (size_t)pl->P * pl->n * pl->ncol * c));
+        PMMM_HIP(hipMalloc(&pl->spec, (size_t)pl->P * pl->nzs * pl->ncol * c));
         if (pl->generic) PMMM_HIP(hipMalloc(&pl->spec2, (size_t)pl->P * pl->n * pl->ncol * c));
     }
     PMMM_HIP(hipMalloc(&pl->M, (size_t)(pl->P + 1) * pl->K * t));
@@ -396,6 +413,24 @@ static int group_for(double mean) {
 
 // What one call computes: the far field (pmmm_far_*), the near field alone
 // (pmmm_near_*) or both with one binning (pmmm_total_*).
+// Sizes and tables of a plan's convolution stages.  An open box's planes
+// [lim z, n) hold no moments and no target, so the stages stop at its top.
+static FFTArgs plan_conv(const Plan *pl) {
+    FFTArgs f{};
+    f.p = pl->p;
+    f.n = pl->n;
+    f.nf = pl->nf;
+    f.nfz = pl->nfz;
+    f.nzs = pl->nzs;
+    f.nzl = pl->open ? pl->lim[2] : pl->n;
+    f.open = pl->open;
+    f.green = pl->green;
+    f.tw = pl->tw;
+    const size_t own = (size_t)(pl->nf / 2) * 2 * pl->tsize;   // a shorter z length's follow
+    f.twz = pl->nfz == pl->nf ? pl->tw : (const char *)pl->tw + own;
+    return f;
+}
+
 // kHierFine / kHierTotal: the fine level of a hierarchy (and its near field),
 // added into outputs that already hold the coarse far field
 enum CallMode { kFar = 0, kNear = 1, kTotal = 2, kHierFine = 3, kHierTotal = 4 };
@@ -559,15 +594,9 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
             m.order = pl->hier_mat ? hier_moment_order(pl->n, pl->hier_r) : 0;
             PMMM_HIP(launch_p2m<T>(m, s));
         }
-        FFTArgs f{};
-        f.p = pl->p;
-        f.n = pl->n;
-        f.nf = pl->nf;
-        f.open = pl->open;
+        FFTArgs f = plan_conv(pl);
         f.M = pl->M;
         f.spec = pl->spec;
-        f.green = pl->green;
-        f.tw = pl->tw;
         f.L = pl->L;
         f.qr2_partial = pl->qr2_partial;
         f.sums = pl->sums;
@@ -911,13 +940,13 @@ static int autotune_impl(pmmm_plan_s *pl, int64_t n, const T *x, const T *y, con
         cand.push_back({0, 0});     // one M2L kernel, no forms to choose from
     } else {
         int wmax = 1, rs = 1;
-        if (column_shape(pl->p, pl->nf, pl->tsize, &wmax, &rs) > 0) {
+        if (column_shape(pl->p, pl->nfz, pl->tsize, &wmax, &rs) > 0) {
             cand.push_back({PMMM_COLUMN_TILE, wmax});
             if (wmax >= 2) cand.push_back({PMMM_COLUMN_TILE, wmax / 2});
             if (wmax >= 4) cand.push_back({PMMM_COLUMN_TILE, wmax / 4});
         }
         for (int kind : {PMMM_COLUMN_STREAM_1, PMMM_COLUMN_STREAM_2, PMMM_COLUMN_STREAM_4})
-            if (column_kernel_fits(kind, pl->p, pl->nf, pl->tsize)) cand.push_back({kind, 0});
+            if (column_kernel_fits(kind, pl->p, pl->nfz, pl->tsize)) cand.push_back({kind, 0});
     }
     if (cand.empty()) return PMMM_EUNSUPPORTED;
     const int gs[4] = {4, 8, 16, 32};
@@ -1064,7 +1093,7 @@ static int batch_alloc_class(BatchClass &c, hipStream_t s) {
     PMMM_HIP(hipMalloc(&c.start, sizeof(int) * (K + 1) * ns));
     PMMM_HIP(hipMalloc(&c.small, sizeof(int) * 8 * ns));
     PMMM_HIP(hipMalloc(&c.M, t * (P + 1) * K * ns));
-    PMMM_HIP(hipMalloc(&c.spec, 2 * t * P * pl->n * pl->ncol * ns));
+    PMMM_HIP(hipMalloc(&c.spec, 2 * t * P * pl->nzs * pl->ncol * ns));
     PMMM_HIP(hipMalloc(&c.L, t * P * K * ns));
     PMMM_HIP(hipMalloc(&c.qr2, sizeof(double) * pl->n * ns));
     PMMM_HIP(hipMalloc(&c.sums, sizeof(double) * 8 * ns));
@@ -1157,15 +1186,9 @@ static int class_enqueue(pmmm_batch_s *b, BatchClass &c, const float *x, const f
         m.prange = c.d_prange;
         m.nsys = ns;
         PMMM_HIP(launch_p2m<float>(m, s));
-        FFTArgs f{};
-        f.p = pl->p;
-        f.n = pl->n;
-        f.nf = pl->nf;
-        f.open = pl->open;
+        FFTArgs f = plan_conv(pl);
         f.M = c.M;
         f.spec = c.spec;
-        f.green = pl->green;
-        f.tw = pl->tw;
         f.L = c.L;
         f.qr2_partial = c.qr2;
         f.sums = c.sums;
@@ -1502,6 +1525,49 @@ int pmmm_hier_sync_status(pmmm_hier h) {
 
 }  // extern "C"
 
+// Stored transfer-kernel values of the plan's whole cube.
+static int64_t cube_green(const Plan *pl) {
+    const int64_t nh = pl->nf / 2 + 1, nhp = (nh + 3) & ~3;
+    return nh * nh * pl->Q * nhp;
+}
+
+// L or the transfer kernel of the whole cube of an open plan whose calls stop
+// at the top of its box: a plan of the cube, its stages run on this plan's
+// moments.
+template <typename T>
+static int copy_cube_mesh(pmmm_plan_s *pl, int which, void *dst, size_t bytes) {
+    pmmm_params prm = pl->prm;
+    prm.nx = prm.ny = prm.nz = pl->n;
+    for (double &b : prm.box) b = pl->box;
+    prm.n_max = 0;
+    int device = 0;
+    PMMM_HIP(hipGetDevice(&device));
+    PMMM_HIP(hipSetDevice(pl->device));
+    pmmm_plan_s *cube = nullptr;
+    int rc = pmmm_plan_create(&prm, nullptr, &cube);
+    if (rc != PMMM_OK) {
+        (void)hipSetDevice(device);
+        return rc;
+    }
+    hipError_t e = hipSuccess;
+    if (which == PMMM_MESH_L) {
+        FFTArgs f = plan_conv(cube);
+        f.M = pl->M;
+        f.spec = cube->spec;
+        f.L = cube->L;
+        f.qr2_partial = cube->qr2_partial;
+        f.sums = cube->sums;
+        for (int st = 0; st < 3 && e == hipSuccess; ++st) e = launch_conv_stage<T>(f, st, nullptr);
+        if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    }
+    if (e == hipSuccess)
+        e = hipMemcpy(dst, which == PMMM_MESH_L ? cube->L : cube->green, bytes, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) rc = hip_fail(e, "mesh of the whole cube");
+    destroy(cube);
+    (void)hipSetDevice(device);
+    return rc;
+}
+
 extern "C" {
 
 int pmmm_plan_create(const pmmm_params *params, void *stream, pmmm_plan *out) {
@@ -1533,6 +1599,7 @@ int pmmm_plan_create(const pmmm_params *params, void *stream, pmmm_plan *out) {
         g.p = pl->p;
         g.n = pl->n;
         g.nf = pl->nf;
+        g.nfz = pl->nfz;
         g.open = pl->open;
         g.cutoff = pl->cutoff;
         g.images = pl->images;
@@ -1755,7 +1822,9 @@ int pmmm_plan_set_tuning(pmmm_plan plan, const pmmm_tuning *in) {
         return PMMM_EINVAL;
     }
     const int kind = in->column_kernel;
-    if (kind != 0 && !column_kernel_fits(kind, plan->p, plan->nf, plan->tsize)) {
+    // what fits the whole cube's z length is taken too (saved for such a plan)
+    if (kind != 0 && !column_kernel_fits(kind, plan->p, plan->nf, plan->tsize) &&
+        !column_kernel_fits(kind, plan->p, plan->nfz, plan->tsize)) {
         set_error("column kernel form unknown or not fitting this plan");
         return PMMM_EINVAL;
     }
@@ -1763,7 +1832,7 @@ int pmmm_plan_set_tuning(pmmm_plan plan, const pmmm_tuning *in) {
         int wmax = 0, rs = 0;
         const int w = in->column_width;
         if (kind != PMMM_COLUMN_TILE || w < 0 || (w & (w - 1)) != 0 ||
-            column_shape(plan->p, plan->nf, plan->tsize, &wmax, &rs) == 0 || w > wmax) {
+            column_shape(plan->p, plan->nfz, plan->tsize, &wmax, &rs) == 0 || w > wmax) {
             set_error("column width needs the tile form and a power of two that fits LDS");
             return PMMM_EINVAL;
         }
@@ -1803,7 +1872,7 @@ size_t pmmm_plan_mesh_bytes(pmmm_plan plan, int which) {
         case PMMM_MESH_L:
             return (size_t)plan->P * plan->K * plan->tsize;
         case PMMM_MESH_GREEN:
-            return (size_t)plan->ngreen * plan->tsize;
+            return (size_t)cube_green(plan) * plan->tsize;
         default:
             return 0;
     }
@@ -1821,6 +1890,9 @@ int pmmm_plan_copy_mesh(pmmm_plan plan, int which, void *host_dst, size_t bytes)
     }
     const void *src = which == PMMM_MESH_M ? plan->M : (which == PMMM_MESH_L ? plan->L : plan->green);
     PMMM_HIP(hipStreamSynchronize(plan->last_stream));
+    if (which != PMMM_MESH_M && plan->open && plan->lim[2] < plan->n)
+        return plan->prec == PMMM_F64 ? copy_cube_mesh<double>(plan, which, host_dst, bytes)
+                                      : copy_cube_mesh<float>(plan, which, host_dst, bytes);
     PMMM_HIP(hipMemcpy(host_dst, src, bytes, hipMemcpyDeviceToHost));
     return PMMM_OK;
 }

@@ -237,7 +237,7 @@ __device__ __forceinline__ void m2l_put(const cplx<T> *res, cplx<T> *ocol, int s
 // registers for a barrier after the last read of buf) and the block's
 // transfer-kernel tile gt[w][Q][nhp] (kz' in [0, nf/2], padded).
 template <int PO, typename T>
-__global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 4) ? 2 : 1) k_column(int nz, int logn, int w, int rs, int ncol,
+__global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 4) ? 2 : 1) k_column(int nz, int nzl, int nfx, int logn, int w, int rs, int ncol,
                                                 int ngroups,
                                                 const T *__restrict__ green,
                                                 cplx<T> *__restrict__ spec,
@@ -248,7 +248,8 @@ __global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 
     constexpr int Q = nreal(2 * PO);
     constexpr int RS = kRowSplit;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int nf = 1 << logn, nh = nf / 2 + 1, nhp = (nh + 3) & ~3, ls = lds_line(nf);
+    const int nf = 1 << logn, nhp = (nf / 2 + 1 + 3) & ~3, ls = lds_line(nf);
+    const int nh = nfx / 2 + 1;                 // kx values; columns (ky, kx)
     const int nfreq = w * nf;
     const int cstride = w * ls;                 // component stride in buf / obuf
     const bool inplace = rs == RS;              // one row subset per thread
@@ -291,7 +292,7 @@ __global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 
         const int ci = small_div(tc, inv_per_col), r4 = tc - ci * per_col;
         const int col = col0 + ci < ncol ? col0 + ci : ncol - 1;
         const int ky = small_div(col, inv_nh), kx = col - ky * nh;
-        const int kyr = ky <= nf / 2 ? ky : nf - ky;
+        const int kyr = ky <= nfx / 2 ? ky : nfx - ky;
         loff = ci * slab + r4 * vec;
         return (kyr * nh + kx) * per_col + r4;
     };
@@ -315,8 +316,8 @@ __global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 
     const int s_z = (tid >> logw) & (nf - 1);
     const int s_b0 = tid >> (logw + logn);
     const int s_db = nthr >> (logw + logn);
-    const bool s_live = s_z < nz && col0 + s_i < ncol;
-    const int s_g = (s_z < nz ? s_z : nz - 1) * ncol + (col0 + s_i < ncol ? col0 + s_i : ncol - 1);
+    const bool s_live = s_z < nzl && col0 + s_i < ncol;
+    const int s_g = (s_z < nzl ? s_z : nzl - 1) * ncol + (col0 + s_i < ncol ? col0 + s_i : ncol - 1);
     auto s_comp = [&](int u) { return s_b0 + u * s_db < P ? s_b0 + u * s_db : P - 1; };
     auto s_load = [&](int u) { return spec[s_comp(u) * nz * ncol + s_g]; };
     auto s_store = [&](int u, cplx<T> v) {
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 
         const bool live = col < ncol;
         const int ky = col / nh;
         const int kzr = kz <= nf / 2 ? kz : nf - kz;
-        const int flip = (ky > nf / 2 ? 1 : 0) | (kz > nf / 2 ? 2 : 0);
+        const int flip = (ky > nfx / 2 ? 1 : 0) | (kz > nf / 2 ? 2 : 0);
         const T *gp = gt + i * slab + kzr;
         const int gstride = nhp;
         const cplx<T> *mp = buf + i * ls + pos;
@@ -429,7 +430,7 @@ __global__ void __launch_bounds__(PO <= 6 ? 512 : 256, (PO == 7 && sizeof(T) == 
     const int o_z = (tid >> logw) & (nz - 1);
     const int o_a0 = tid >> (logw + lognz);
     const int o_da = nthr >> (logw + lognz);
-    const bool o_live = col0 + o_i < ncol;
+    const bool o_live = col0 + o_i < ncol && o_z < nzl;
     for (int u0 = 0; o_a0 + u0 * o_da < P; u0 += kColumnLoadBatch) {
         cplx<T> v[kColumnLoadBatch];
 #pragma unroll
@@ -566,7 +567,7 @@ __device__ __forceinline__ void m2l_rows_g(const GSlab &gs, int flip,
 // the discarded half of the inverse ones.
 template <int PO, typename T, int RSP, int LOGN>
 __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T) == 4 ? 3 : 2) : (RSP == 4 ? 2 : 1))
-    k_column_g(int nz, int ncol, int ngroups, const T *__restrict__ green,
+    k_column_g(int nz, int nzl, int nfx, int ncol, int ngroups, const T *__restrict__ green,
                cplx<T> *__restrict__ spec, const cplx<T> *__restrict__ tw_g, int periodic,
                const double *__restrict__ qr2_partial, double *__restrict__ sums) {
     constexpr int P = nreal(PO);
@@ -574,7 +575,7 @@ __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T)
     constexpr int RS = kRowSplit;
     constexpr int NSUB = RS / RSP;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    constexpr int logn = LOGN, nf = 1 << LOGN, nh = nf / 2 + 1, nhp = (nh + 3) & ~3, ls = nf;
+    constexpr int logn = LOGN, nf = 1 << LOGN, nhp = (nf / 2 + 1 + 3) & ~3, ls = nf;
     const bool half = 2 * nz == nf;
     cplx<T> *tw = (cplx<T> *)lds_raw;
     cplx<T> *buf = tw + nf;
@@ -596,7 +597,7 @@ __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T)
     const int s_b0 = tid >> logn;
     constexpr int s_db = nthr >> logn;
     const bool s_live = s_z < nz;
-    const int s_g = (s_z < nz ? s_z : nz - 1) * ncol + col;
+    const int s_g = (s_z < nzl ? s_z : nzl - 1) * ncol + col;
     auto s_comp = [&](int u) { return s_b0 + u * s_db < P ? s_b0 + u * s_db : P - 1; };
     constexpr int SB = 2 * kColumnLoadBatch;
     {
@@ -611,7 +612,7 @@ __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T)
 #pragma unroll
                 for (int u = 0; u < SB; ++u) {
                     const int c = s_comp(u0 + u);
-                    buf[c * ls + cpos(c, s_z)] = sv[u];
+                    buf[c * ls + cpos(c, s_z)] = s_z < nzl ? sv[u] : cplx<T>{T(0), T(0)};
                 }
             }
         }
@@ -640,10 +641,11 @@ __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T)
         if (sub == 0) sums[0] = m0(0);  // total charge
     }
     {
+        const int nh = nfx / 2 + 1;
         const int ky = small_div(col, 1.0f / (float)nh), kx = col - ky * nh;
-        const int kyr = ky <= nf / 2 ? ky : nf - ky;
+        const int kyr = ky <= nfx / 2 ? ky : nfx - ky;
         const int kzr = kz <= nf / 2 ? kz : nf - kz;
-        const int flip = (ky > nf / 2 ? 1 : 0) | (kz > nf / 2 ? 2 : 0);
+        const int flip = (ky > nfx / 2 ? 1 : 0) | (kz > nf / 2 ? 2 : 0);
         const GSlab gs = make_gslab<T>(green + (int64_t)(kyr * nh + kx) * Q * nhp, Q * nhp, kzr, nhp);
         // row b of the thread's frequency sits at buf + b * ls + kpos (+ odd
         // for odd b)
@@ -684,7 +686,7 @@ __global__ void __launch_bounds__((kRowSplit / RSP) * 128, RSP == 2 ? (sizeof(T)
 #pragma unroll
         for (int u = 0; u < kColumnLoadBatch; ++u) {
             const int a = o_a0 + (u0 + u) * o_da;
-            if (a < P) spec[(a * nz + o_z) * ncol + col] = v[u];
+            if (a < P && o_z < nzl) spec[(a * nz + o_z) * ncol + col] = v[u];
         }
     }
 }
@@ -698,9 +700,10 @@ inline int column_ilog2(int v) {
 
 template <int PO, typename T, int RSP, int LOGN>
 hipError_t column_launch_g(const FFTArgs &a, hipStream_t s) {
-    constexpr int nf = 1 << LOGN, nh = nf / 2 + 1, ncol = nf * nh;
+    constexpr int nf = 1 << LOGN;
+    const int ncol = a.nf * (a.nf / 2 + 1);
     const size_t lds = column_g_lds(PO, nf, sizeof(T));
-    if (lds == 0 || a.nf != nf || (a.n != nf && 2 * a.n != nf)) return hipErrorInvalidValue;
+    if (lds == 0 || a.nfz != nf || (a.nzs != nf && 2 * a.nzs != nf)) return hipErrorInvalidValue;
     const int threads = (kRowSplit / RSP) * nf;
     if (threads < 64) return hipErrorInvalidValue;
     const int grid = ((ncol + 7) / 8) * 8;
@@ -708,8 +711,8 @@ hipError_t column_launch_g(const FFTArgs &a, hipStream_t s) {
         lds <= 65536 ? hipSuccess : set_max_lds((const void *)k_column_g<PO, T, RSP, LOGN>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_column_g<PO, T, RSP, LOGN>), dim3(grid, a.nsys > 0 ? a.nsys : 1),
-                       dim3(threads), lds, s, a.n, ncol, ncol, (const T *)a.green,
-                       (cplx<T> *)a.spec, (const cplx<T> *)a.tw, a.open ? 0 : 1, a.qr2_partial,
+                       dim3(threads), lds, s, a.nzs, a.nzl, a.nf, ncol, ncol,
+                       (const T *)a.green, (cplx<T> *)a.spec, (const cplx<T> *)a.twz, a.open ? 0 : 1, a.qr2_partial,
                        a.sums);
     return hipGetLastError();
 }
@@ -719,14 +722,16 @@ hipError_t column_launch_g(const FFTArgs &a, hipStream_t s) {
 template <int PO, typename T, int RSP>
 hipError_t column_launch_g(const FFTArgs &a, hipStream_t s) {
     if constexpr (sizeof(T) == 4)
-        if (a.nf == 128) return column_launch_g<PO, T, RSP, 7>(a, s);
-    if (a.nf == 64) return column_launch_g<PO, T, RSP, 6>(a, s);
+        if (a.nfz == 128) return column_launch_g<PO, T, RSP, 7>(a, s);
+    if (a.nfz == 64) return column_launch_g<PO, T, RSP, 6>(a, s);
     return hipErrorInvalidValue;
 }
 
 template <int PO, typename T>
 hipError_t column_launch(const FFTArgs &a, hipStream_t s) {
-    const int kind = a.col_kernel > 0 ? a.col_kernel : column_default_kernel(PO, a.nf, sizeof(T));
+    // a tuned form that does not take this z length gives way to the default
+    const int kind = a.col_kernel > 0 && column_kernel_fits(a.col_kernel, PO, a.nfz, sizeof(T))
+                         ? a.col_kernel : column_default_kernel(PO, a.nfz, sizeof(T));
     switch (kind) {
         case PMMM_COLUMN_STREAM_1: return column_launch_g<PO, T, 1>(a, s);
         case PMMM_COLUMN_STREAM_2:
@@ -738,7 +743,7 @@ hipError_t column_launch(const FFTArgs &a, hipStream_t s) {
         case PMMM_COLUMN_TILE: break;
         default: return hipErrorInvalidValue;
     }
-    const int nf = a.nf, logn = column_ilog2(nf), nh = nf / 2 + 1, ncol = nf * nh;
+    const int nf = a.nfz, logn = column_ilog2(nf), ncol = a.nf * (a.nf / 2 + 1);
     int w = 1, rs = 1;
     size_t lds = column_shape(PO, nf, sizeof(T), &w, &rs);
     if (lds == 0) return hipErrorInvalidValue;
@@ -754,9 +759,10 @@ hipError_t column_launch(const FFTArgs &a, hipStream_t s) {
     const int grid = ((ngroups + 7) / 8) * 8;
     hipError_t e = lds <= 65536 ? hipSuccess : set_max_lds((const void *)k_column<PO, T>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_column<PO, T>), dim3(grid, a.nsys > 0 ? a.nsys : 1), dim3(threads), lds, s, a.n, logn, w, rs,
+    hipLaunchKernelGGL((k_column<PO, T>), dim3(grid, a.nsys > 0 ? a.nsys : 1), dim3(threads), lds, s,
+                       a.nzs, a.nzl, a.nf, logn, w, rs,
                        ncol, ngroups, (const T *)a.green, (cplx<T> *)a.spec,
-                       (const cplx<T> *)a.tw, a.open ? 0 : 1, a.qr2_partial, a.sums);
+                       (const cplx<T> *)a.twz, a.open ? 0 : 1, a.qr2_partial, a.sums);
     return hipGetLastError();
 }
 

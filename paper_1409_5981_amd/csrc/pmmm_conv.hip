@@ -51,7 +51,7 @@ __global__ void __launch_bounds__(512) k_plane_fwd(int nin, int logn,
                                                    cplx<T> *__restrict__ spec,
                                                    const cplx<T> *__restrict__ tw_g,
                                                    int P, double *__restrict__ qr2_partial,
-                                                   int cw, int cws, int cpb) {
+                                                   int cw, int cws, int cpb, int nzs) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const int nf = 1 << logn, nh = nf / 2 + 1, npair = nin / 2, ls = lds_line(nf);
     const int z = blockIdx.x;
@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(512) k_plane_fwd(int nin, int logn,
         // system blockIdx.z of a batch: meshes at fixed strides
         const int64_t sy = blockIdx.z, K = (int64_t)nin * nin * nin;
         M += sy * (P + 1) * K;
-        spec += sy * P * nin * nf * nh;
+        spec += sy * P * nzs * nf * nh;
         if (qr2_partial != nullptr) qr2_partial += sy * nin;
     }
     if ((int)blockIdx.y == (P + cpb - 1) / cpb) {
@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(512) k_plane_fwd(int nin, int logn,
     if (tid < nf / 2) tw[tid] = twv;
     __syncthreads();
     fft_lines<T, false>(buf1, logn, npair, ls, 1, tw, tid, nthr);
-    cplx<T> *out = spec + ((int64_t)c * nin + z) * nf * nh;
+    cplx<T> *out = spec + ((int64_t)c * nzs + z) * nf * nh;
     // y FFTs: all nh kx columns at once, or in chunks of cw when LDS is short
     if (cw >= nh) {
         for (int idx = tid; idx < nf * nh; idx += nthr) {
@@ -151,12 +151,12 @@ __global__ void __launch_bounds__(512) k_plane_inv(int nout, int logn,
                                                    const cplx<T> *__restrict__ spec,
                                                    T *__restrict__ L,
                                                    const cplx<T> *__restrict__ tw_g, T scale,
-                                                   int P, int cw, int cws, int cpb) {
+                                                   int P, int cw, int cws, int cpb, int nzs) {
     {
         // system blockIdx.z of a batch: meshes at fixed strides
         const int64_t sy = blockIdx.z;
         const int nf_ = 1 << logn;
-        spec += sy * P * nout * nf_ * (nf_ / 2 + 1);
+        spec += sy * P * nzs * nf_ * (nf_ / 2 + 1);
         L += sy * P * nout * nout * nout;
     }
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(512) k_plane_inv(int nout, int logn,
     cplx<T> *buf1 = buf2 + nf * cws;       // [npair][ls]
     // twiddle load in flight together with the spectrum's (nf/2 <= blockDim.x)
     const cplx<T> twv = tw_g[tid < nf / 2 ? tid : 0];
-    const cplx<T> *in = spec + ((int64_t)c * nout + z) * nf * nh;
+    const cplx<T> *in = spec + ((int64_t)c * nzs + z) * nf * nh;
     // y inverse FFTs: all nh kx columns at once, or in chunks of cw when LDS
     // is short; the results are packed into the C2R rows of buf1 (columns kx
     // and nf - kx of a row pair come from column kx)
@@ -265,7 +265,7 @@ template <typename T, int N, bool HALF>
 __global__ void __launch_bounds__(kPlaneThreads) k_plane_fwd_n(const T *__restrict__ M,
                                                                cplx<T> *__restrict__ spec,
                                                                const cplx<T> *__restrict__ tw_g,
-                                                               int P,
+                                                               int P, int nzs,
                                                                double *__restrict__ qr2_partial) {
     constexpr int nin = HALF ? N / 2 : N, npair = nin / 2, nh = N / 2 + 1, N2 = N / 16;
     constexpr int CWS = kPlaneChunk;  // odd row stride of yb
@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(kPlaneThreads) k_plane_fwd_n(const T *__restri
     {
         const int64_t sy = blockIdx.z, K = (int64_t)nin * nin * nin;
         M += sy * (P + 1) * K;
-        spec += sy * P * nin * N * nh;
+        spec += sy * P * nzs * N * nh;
         if (qr2_partial != nullptr) qr2_partial += sy * nin;
     }
     if ((int)blockIdx.y == P) {
@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(kPlaneThreads) k_plane_fwd_n(const T *__restri
     fill_twiddles<T>(tw, tw_g, N, tid, kPlaneThreads);
     __syncthreads();
     fft_col<T, false, N, HALF>(xb, npair, tw, tid, kPlaneThreads);   // ends with a barrier
-    cplx<T> *out = spec + ((int64_t)c * nin + z) * N * nh;
+    cplx<T> *out = spec + ((int64_t)c * nzs + z) * N * nh;
     for (int k0 = 0; k0 < nh; k0 += kPlaneChunk) {
         const int cn = nh - k0 < kPlaneChunk ? nh - k0 : kPlaneChunk;
         // y transforms, first step: 16-point FFTs over n1 of x[n1 N2 + t2]
@@ -374,7 +374,7 @@ template <typename T, int N, bool HALF>
 __global__ void __launch_bounds__(kPlaneThreads) k_plane_inv_n(const cplx<T> *__restrict__ spec,
                                                                T *__restrict__ L,
                                                                const cplx<T> *__restrict__ tw_g,
-                                                               T scale, int P) {
+                                                               T scale, int P, int nzs) {
     constexpr int nout = HALF ? N / 2 : N, npair = nout / 2, nh = N / 2 + 1, N2 = N / 16;
     constexpr int CWS = kPlaneChunk;
     constexpr int K2 = HALF ? N2 / 2 : N2;   // y rows kept: k2 * 16 + k1 < nout
@@ -385,12 +385,12 @@ __global__ void __launch_bounds__(kPlaneThreads) k_plane_inv_n(const cplx<T> *__
     const int z = blockIdx.x, c = blockIdx.y, tid = threadIdx.x;
     {
         const int64_t sy = blockIdx.z;
-        spec += sy * P * nout * N * nh;
+        spec += sy * P * nzs * N * nh;
         L += sy * P * nout * nout * nout;
     }
     fill_twiddles<T>(tw, tw_g, N, tid, kPlaneThreads);
     __syncthreads();
-    const cplx<T> *in = spec + ((int64_t)c * nout + z) * N * nh;
+    const cplx<T> *in = spec + ((int64_t)c * nzs + z) * N * nh;
     for (int k0 = 0; k0 < nh; k0 += kPlaneChunk) {
         const int cn = nh - k0 < kPlaneChunk ? nh - k0 : kPlaneChunk;
         // y inverse transforms, first step, straight from memory (lanes take
@@ -462,7 +462,7 @@ static size_t plane_n_lds(bool half) {
 
 template <typename T, int N>
 static hipError_t plane_n_launch(const FFTArgs &a, int stage, hipStream_t s) {
-    const int P = nreal(a.p), n = a.n, nsys = a.nsys > 0 ? a.nsys : 1;
+    const int P = nreal(a.p), nz = a.nzl, nsys = a.nsys > 0 ? a.nsys : 1;
     const bool half = a.open != 0;
     const size_t lds = plane_n_lds<T, N>(half);
     hipError_t e = hipSuccess;
@@ -472,26 +472,26 @@ static hipError_t plane_n_launch(const FFTArgs &a, int stage, hipStream_t s) {
         if (lds > 65536 && (e = set_max_lds(k, lds)) != hipSuccess) return e;
         const int rows = half ? P : P + 1;   // periodic: one extra row of q|u|^2 sums
         if (half)
-            hipLaunchKernelGGL((k_plane_fwd_n<T, N, true>), dim3(n, rows, nsys),
+            hipLaunchKernelGGL((k_plane_fwd_n<T, N, true>), dim3(nz, rows, nsys),
                                dim3(kPlaneThreads), lds, s, (const T *)a.M, (cplx<T> *)a.spec,
-                               (const cplx<T> *)a.tw, P, nullptr);
+                               (const cplx<T> *)a.tw, P, a.nzs, nullptr);
         else
-            hipLaunchKernelGGL((k_plane_fwd_n<T, N, false>), dim3(n, rows, nsys),
+            hipLaunchKernelGGL((k_plane_fwd_n<T, N, false>), dim3(nz, rows, nsys),
                                dim3(kPlaneThreads), lds, s, (const T *)a.M, (cplx<T> *)a.spec,
-                               (const cplx<T> *)a.tw, P, a.qr2_partial);
+                               (const cplx<T> *)a.tw, P, a.nzs, a.qr2_partial);
     } else {
         const void *k = half ? (const void *)k_plane_inv_n<T, N, true>
                              : (const void *)k_plane_inv_n<T, N, false>;
         if (lds > 65536 && (e = set_max_lds(k, lds)) != hipSuccess) return e;
-        const T scale = T(1.0 / ((double)N * N * N));
+        const T scale = T(1.0 / ((double)N * N * a.nfz));
         if (half)
-            hipLaunchKernelGGL((k_plane_inv_n<T, N, true>), dim3(n, P, nsys), dim3(kPlaneThreads),
+            hipLaunchKernelGGL((k_plane_inv_n<T, N, true>), dim3(nz, P, nsys), dim3(kPlaneThreads),
                                lds, s, (const cplx<T> *)a.spec, (T *)a.L, (const cplx<T> *)a.tw,
-                               scale, P);
+                               scale, P, a.nzs);
         else
-            hipLaunchKernelGGL((k_plane_inv_n<T, N, false>), dim3(n, P, nsys), dim3(kPlaneThreads),
+            hipLaunchKernelGGL((k_plane_inv_n<T, N, false>), dim3(nz, P, nsys), dim3(kPlaneThreads),
                                lds, s, (const cplx<T> *)a.spec, (T *)a.L, (const cplx<T> *)a.tw,
-                               scale, P);
+                               scale, P, a.nzs);
     }
     return hipGetLastError();
 }
@@ -525,12 +525,12 @@ struct PlaneShape {
     int threads, cw, cws, cpb;
     size_t lds;
 };
-static PlaneShape plane_shape(int n, int nf, int P, int nsys, size_t csz) {
+static PlaneShape plane_shape(int n, int nz, int nf, int P, int nsys, size_t csz) {
     const int nh = nf / 2 + 1;
     PlaneShape ps;
     ps.threads = 256;
     ps.cpb = nf <= 16 ? 8 : (nf == 32 ? 4 : (nf == 64 ? 2 : 1));
-    if ((int64_t)n * P * nsys < 1024) ps.cpb = 1;
+    if ((int64_t)nz * P * nsys < 1024) ps.cpb = 1;
     ps.cw = nf >= 128 ? 16 : nh;
     ps.cws = ps.cw == nh ? nh : ps.cw + 1;
     ps.lds = (size_t)(nf / 2 + ps.cpb * ((n / 2) * lds_line(nf) + nf * ps.cws)) * csz;
@@ -541,10 +541,10 @@ template <typename T>
 hipError_t launch_conv_stage(const FFTArgs &a, int stage, hipStream_t s) {
     if (a.generic) return launch_generic_stage<T>(a, stage, s);
     const int P = nreal(a.p);
-    const int nf = a.nf, logn = ilog2(nf), nh = nf / 2 + 1, n = a.n;
+    const int nf = a.nf, logn = ilog2(nf), n = a.n;
     const int nsys = a.nsys > 0 ? a.nsys : 1;
     const size_t csz = sizeof(cplx<T>);
-    const PlaneShape ps = plane_shape(n, nf, P, nsys, csz);
+    const PlaneShape ps = plane_shape(n, a.nzl, nf, P, nsys, csz);
     const size_t lds_plane = ps.lds;
     hipError_t e = hipSuccess;
     if (stage != 1 && (nf == 64 || nf == 128)) {
@@ -557,9 +557,9 @@ hipError_t launch_conv_stage(const FFTArgs &a, int stage, hipStream_t s) {
         // periodic: one extra row of blocks sums q|u|^2 per plane
         const int crows = (P + ps.cpb - 1) / ps.cpb;
         const int rows = a.open ? crows : crows + 1;
-        hipLaunchKernelGGL(k_plane_fwd<T>, dim3(n, rows, nsys), dim3(ps.threads), lds_plane, s, n,
+        hipLaunchKernelGGL(k_plane_fwd<T>, dim3(a.nzl, rows, nsys), dim3(ps.threads), lds_plane, s, n,
                            logn, (const T *)a.M, (cplx<T> *)a.spec, (const cplx<T> *)a.tw, P,
-                           a.open ? nullptr : a.qr2_partial, ps.cw, ps.cws, ps.cpb);
+                           a.open ? nullptr : a.qr2_partial, ps.cw, ps.cws, ps.cpb, a.nzs);
         return hipGetLastError();
     }
     if (stage == 1) {
@@ -580,10 +580,10 @@ hipError_t launch_conv_stage(const FFTArgs &a, int stage, hipStream_t s) {
     }
     e = ensure_lds(k_plane_inv<T>, lds_plane);
     if (e != hipSuccess) return e;
-    const T scale = T(1.0 / ((double)nf * nf * nf));
-    hipLaunchKernelGGL(k_plane_inv<T>, dim3(n, (P + ps.cpb - 1) / ps.cpb, nsys), dim3(ps.threads),
+    const T scale = T(1.0 / ((double)nf * nf * a.nfz));
+    hipLaunchKernelGGL(k_plane_inv<T>, dim3(a.nzl, (P + ps.cpb - 1) / ps.cpb, nsys), dim3(ps.threads),
                        lds_plane, s, n, logn, (const cplx<T> *)a.spec, (T *)a.L,
-                       (const cplx<T> *)a.tw, scale, P, ps.cw, ps.cws, ps.cpb);
+                       (const cplx<T> *)a.tw, scale, P, ps.cw, ps.cws, ps.cpb, a.nzs);
     return hipGetLastError();
 }
 

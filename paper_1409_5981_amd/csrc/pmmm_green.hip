@@ -68,16 +68,17 @@ __device__ void singular_tri(int lmax, double x, double y, double z, double *sre
     }
 }
 
-__global__ void k_green_open(int n, int nf, int lmax, int cutoff, double *__restrict__ G) {
-    const int64_t npts = (int64_t)nf * nf * nf;
+__global__ void k_green_open(int n, int nf, int nfz, int lmax, int cutoff, double *__restrict__ G) {
+    const int64_t npts = (int64_t)nf * nf * nfz;
+    const int nz = nfz / 2;
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= npts) return;
     const int ix = (int)(idx % nf), iy = (int)((idx / nf) % nf), iz = (int)(idx / ((int64_t)nf * nf));
     const int Q = (lmax + 1) * (lmax + 1);
-    const int dx = ix < n ? ix : ix - nf, dy = iy < n ? iy : iy - nf, dz = iz < n ? iz : iz - nf;
+    const int dx = ix < n ? ix : ix - nf, dy = iy < n ? iy : iy - nf, dz = iz < nz ? iz : iz - nfz;
     int cheb = abs(dx) > abs(dy) ? abs(dx) : abs(dy);
     cheb = cheb > abs(dz) ? cheb : abs(dz);
-    const bool zero = ix == n || iy == n || iz == n || cheb <= cutoff;
+    const bool zero = ix == n || iy == n || iz == nz || cheb <= cutoff;
     if (zero) {
         for (int j = 0; j < Q; ++j) G[(int64_t)j * npts + idx] = 0.0;
         return;
@@ -261,17 +262,17 @@ __global__ void __launch_bounds__(64) k_line_fft(cplx<double> *__restrict__ data
     }
 }
 
-// Keeps Re G~ (even order) or Im G~ (odd order) for ky, kz in [0, nf/2]
+// Keeps Re G~ (even order) or Im G~ (odd order) for ky in [0, nf/2], kz in [0, nfz/2]
 // (the other quadrants follow from the y and z reflection symmetries of
-// S_n^k), layout [ky' * nh + kx][Q][nhp] with nh = nf/2 + 1 and nhp = nh
+// S_n^k), layout [ky' * nh + kx][Q][nhp] with nh = nf/2 + 1 and nhp = nfz/2 + 1
 // rounded up to 4 (padding zero).  self_shift is added to component 0 at
 // every frequency: a kernel weight at offset zero, i.e. the self term
 // -(2 alpha/sqrt(pi)) M_0^0(cell) of the periodic correction procedure
 // (App. B) applied inside the convolution.
 template <typename T>
-__global__ void k_fold(int nf, int Q, int j0, int jcount, const cplx<double> *__restrict__ Gc,
+__global__ void k_fold(int nf, int nfz, int Q, int j0, int jcount, const cplx<double> *__restrict__ Gc,
                        double self_shift, T *__restrict__ out) {
-    const int nh = nf / 2 + 1, nhp = (nh + 3) & ~3;
+    const int nh = nf / 2 + 1, nhz = nfz / 2 + 1, nhp = (nhz + 3) & ~3;
     const int64_t total = (int64_t)nh * nh * jcount * nhp;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= total) return;
@@ -283,8 +284,8 @@ __global__ void k_fold(int nf, int Q, int j0, int jcount, const cplx<double> *__
     int order = 0;
     while ((order + 1) * (order + 1) <= j) ++order;
     double g = 0.0;
-    if (kz < nh) {
-        const cplx<double> v = Gc[(((int64_t)jl * nf + kz) * nf + ky) * nf + kx];
+    if (kz < nhz) {
+        const cplx<double> v = Gc[(((int64_t)jl * nfz + kz) * nf + ky) * nf + kx];
         g = (order & 1) ? v.im : v.re + (j == 0 ? self_shift : 0.0);
     }
     out[(colr * Q + j) * nhp + kz] = T(g);
@@ -299,8 +300,8 @@ static int ilog2i(int v) {
 template <typename T>
 hipError_t build_green(const GreenArgs &a, hipStream_t s) {
     const int lmax = 2 * a.p, Q = (lmax + 1) * (lmax + 1);
-    const int nf = a.nf, logn = ilog2i(nf);
-    const int64_t npts = (int64_t)nf * nf * nf;
+    const int nf = a.nf, nfz = a.nfz;
+    const int64_t npts = (int64_t)nf * nf * nfz;
     double *G = nullptr;
     cplx<double> *Gc = nullptr, *tw = nullptr;
     int *kvec = nullptr;
@@ -320,6 +321,9 @@ hipError_t build_green(const GreenArgs &a, hipStream_t s) {
     std::vector<cplx<double>> twh(ntw);
     for (int k = 0; k < ntw; ++k)
         twh[k] = {std::cos(2.0 * M_PI * k / nf), -std::sin(2.0 * M_PI * k / nf)};
+    if (pow2 && nfz != nf)       // the z transform's twiddles behind them
+        for (int k = 0; k < nfz / 2; ++k)
+            twh.push_back({std::cos(2.0 * M_PI * k / nfz), -std::sin(2.0 * M_PI * k / nfz)});
     e = hipMalloc(&tw, sizeof(cplx<double>) * twh.size());
     if (e == hipSuccess)
         e = hipMemcpyAsync(tw, twh.data(), sizeof(cplx<double>) * twh.size(),
@@ -327,7 +331,7 @@ hipError_t build_green(const GreenArgs &a, hipStream_t s) {
     if (e == hipSuccess) {
         const int blocks = (int)((npts + 127) / 128);
         if (a.open) {
-            hipLaunchKernelGGL(k_green_open, dim3(blocks), dim3(128), 0, s, a.n, nf, lmax,
+            hipLaunchKernelGGL(k_green_open, dim3(blocks), dim3(128), 0, s, a.n, nf, nfz, lmax,
                                a.cutoff, G);
         } else {
             std::vector<int> kv;
@@ -364,18 +368,20 @@ hipError_t build_green(const GreenArgs &a, hipStream_t s) {
                            cnt, G + (int64_t)j0 * npts, Gc);
         for (int axis = 0; axis < 3 && e == hipSuccess; ++axis) {
             const int64_t stride = axis == 0 ? 1 : (axis == 1 ? nf : (int64_t)nf * nf);
-            const int64_t nlines = (int64_t)jc * nf * nf;
+            const int len = axis == 2 ? nfz : nf;
+            const int64_t nlines = (int64_t)jc * npts / len;
             if (pow2)
                 hipLaunchKernelGGL(k_line_fft, dim3((unsigned)((nlines + lpb - 1) / lpb)),
-                                   dim3(64), lds, s, Gc, logn, nlines, stride, lpb, tw);
+                                   dim3(64), lds, s, Gc, ilog2i(len), nlines, stride, lpb,
+                                   len == nf ? tw : tw + ntw);
             else
                 e = launch_line_dft_f64(Gc, nf, nlines, stride, tw, s);
         }
-        const int nhp = ((nf / 2 + 1) + 3) & ~3;
+        const int nhp = ((nfz / 2 + 1) + 3) & ~3;
         const int64_t tot = (int64_t)(nf / 2 + 1) * (nf / 2 + 1) * jc * nhp;
         const double shift = a.open ? 0.0 : -2.0 * a.alpha_cell / std::sqrt(M_PI);
         if (e != hipSuccess) break;
-        hipLaunchKernelGGL(k_fold<T>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, nf, Q,
+        hipLaunchKernelGGL(k_fold<T>, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, nf, nfz, Q,
                            j0, jc, Gc, shift, (T *)a.green_out);
         e = hipGetLastError();
     }

@@ -731,10 +731,12 @@ struct FFTArgs {
     int p, n, nf, open;
     double *qr2_partial;            // [n] per-plane sums of q|u|^2 (periodic)
     double *sums;                   // [0] = total charge (periodic, for L2P)
+    int nfz, nzs, nzl;              // z transform length, spectra planes, planes of the caller's box
     const void *M;                  // [P(+1)][n^3] real mesh
-    void *spec;                     // [P][n][nf][nf/2+1] complex
-    const void *green;              // [nf*(nf/2+1)][Q][nf]
+    void *spec;                     // [P][nzs][nf][nf/2+1] complex
+    const void *green;              // [nf*(nf/2+1)][Q][nfz]
     const void *tw;                 // cplx<T>[nf/2]
+    const void *twz;                // cplx<T>[nfz/2]
     void *L;                        // [P][n^3]
     int nsys;                       // batch of systems at fixed strides (1: one)
     int col_w;                      // columns per column-kernel block (0: largest that fits)
@@ -802,9 +804,9 @@ hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s);
 
 // Plan-time transfer kernel (FP64 on the GPU), stored in precision T.
 struct GreenArgs {
-    int p, n, nf, open, cutoff, images;
+    int p, n, nf, nfz, open, cutoff, images;
     double alpha_cell;              // alpha h
-    void *green_out;                // [nf*(nf/2+1)][Q][nf] in T
+    void *green_out;                // [nf*(nf/2+1)][Q][nfz] in T
 };
 template <typename T>
 hipError_t build_green(const GreenArgs &a, hipStream_t s);

@@ -185,3 +185,64 @@ def test_periodic_non_power_of_two_autotune():
     ref = opm.far_field(pos.astype(np.float64), q.astype(np.float64), cfg)
     res = _pgpu(pos, q, n, p, box, "f32", 2, autotune=True)
     assert_parity(res, ref.phi, ref.grad, "f32", "periodic n=12 autotuned")
+
+
+# ---------------------------------- flat open boxes: shorter z transforms
+# The z transform holds the box's own z extent (16, 32 or 64 points of 32, 64
+# or 128 along x and y; 40 x 36 x 33 keeps all 128) and the stages stop at the
+# box's top plane (below the transform's last one in all but (16, 12, 8)).
+@pytest.mark.parametrize("dims,p,precision,cutoff,n", [
+    ((16, 12, 8), 5, "f32", 2, 4000),
+    ((30, 20, 15), 6, "f32", 2, 6000),
+    ((18, 17, 7), 4, "f64", 1, 3000),
+    ((40, 21, 9), 2, "f32", 2, 5000),
+    ((34, 40, 19), 3, "f32", 1, 6000),
+    ((40, 36, 33), 2, "f32", 2, 6000),
+])
+def test_open_flat_boxes_match_oracle(dims, p, precision, cutoff, n):
+    dt = np.float32 if precision == "f32" else np.float64
+    print(f"flat {dims} p={p} {precision} c={cutoff} n={n}", flush=True)
+    pos, q, box = _set(dims, n, sum(dims) + p, dt)
+    cfg = opm.Config(n=dims[0], p=p, boundary="open", box=box, cutoff=cutoff, shape=dims)
+    ref = opm.far_field(pos.astype(np.float64), q.astype(np.float64), cfg)
+    res, _, st = _gpu(pos, q, dims, p, box, precision, cutoff)
+    assert st == 0
+    assert_parity(res, ref.phi, ref.grad, precision, f"flat {dims} p={p}")
+
+
+@pytest.mark.parametrize("dims,p", [((32, 30, 20), 4), ((40, 36, 24), 3)])
+def test_open_flat_box_tunings_and_meshes(dims, p):
+    """Every column form that the whole cube takes is taken by the flat plan
+    and by the autotuner's result; the meshes are the whole cube's."""
+    import torch
+    from paper_1409_5981_amd._lib import (COLUMN_KERNELS, PMMM_MESH_GREEN, PMMM_MESH_L, PMMM_MESH_M,
+                                          Plan, PMMMError)
+    pos, q, box = _set(dims, 5000, 11, np.float32)
+    cfg = opm.Config(n=dims[0], p=p, boundary="open", box=box, cutoff=2, shape=dims)
+    ref = opm.far_field(pos.astype(np.float64), q.astype(np.float64), cfg)
+    _, plan, _ = _gpu(pos, q, dims, p, box, "f32", 2)
+    n = plan.n_mesh
+    cube = Plan(n, p, "open", box=box / dims[0] * n, cutoff=2)
+    t = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (*pos.T, q)]
+    cube.far(*t)
+    torch.cuda.synchronize()
+    for which in (PMMM_MESH_M, PMMM_MESH_GREEN, PMMM_MESH_L):
+        assert np.array_equal(plan.mesh(which), cube.mesh(which)), which
+    for kind in COLUMN_KERNELS:
+        try:
+            cube.set_tuning(kind)
+        except PMMMError:
+            continue
+        plan.set_tuning(kind)
+        out = plan.far(*t)
+        torch.cuda.synchronize()
+        res = {"phi": out[0].double().cpu().numpy(),
+               "grad": torch.stack(list(out[1:]), 1).double().cpu().numpy()}
+        assert_parity(res, ref.phi, ref.grad, "f32", f"flat {dims} {kind}")
+    kept = plan.autotune(*t)
+    plan.set_tuning(**kept)
+    out = plan.far(*t)
+    torch.cuda.synchronize()
+    res = {"phi": out[0].double().cpu().numpy(),
+           "grad": torch.stack(list(out[1:]), 1).double().cpu().numpy()}
+    assert_parity(res, ref.phi, ref.grad, "f32", f"flat {dims} autotuned")
