@@ -20,218 +20,165 @@
 
 namespace pmmm {
 
-// Global loads each thread keeps in flight before writing them to LDS.
-constexpr int kLoadBatch = 8;
-
 // ------------------------------------------------------------------ planes
-// Row y, column k of the x spectra from the packed FFT of the row pair
-// (y & ~1, y | 1) held as one complex row (zero rows y >= nin).
+// ------------------------------------------------- planes up to 32 points
+// FFT sizes N = 4 to 32: a block takes pb planes (component c, z), one wave or
+// two.  Every transform of a plane is one thread's, in registers: N/2 (open:
+// N/4) row pairs along x -- two real rows as one complex row -- and N/2 + 1
+// columns along y, so that pb (N/2 + 1) fills the block's lanes (planes_per).
+// The planes pass through LDS twice, rows of N + 1 values against bank
+// conflicts, and the spectra go straight between registers and memory.  Bound
+// by HBM: each plane is read and written once.  Measured against the block-wide
+// passes this replaced (a barrier per FFT step, 256 threads on up to 8 planes):
+// periodic 32^3, p = 7, 2048 planes 14.6 -> 9.3 us forward, 16.1 -> 8.3 inverse
+// (17 MB each way, 3.7 us); batch of 256 systems of 8^3 to 32^3 cells, whole
+// call 2835 -> 2156 us; FP64 open 16^3, p = 5, whole call 79 -> 61.
 template <typename T>
-__device__ __forceinline__ cplx<T> unpack_row_pair(const cplx<T> *buf1, int ls, int nf, int nin,
-                                                   int y, int k) {
-    cplx<T> v = {T(0), T(0)};
-    if (y < nin) {
-        const cplx<T> *row = buf1 + (y >> 1) * ls;
-        const cplx<T> zk = row[k & (nf - 1)];
-        const cplx<T> zm = row[(nf - k) & (nf - 1)];
-        if ((y & 1) == 0) {
-            v.re = T(0.5) * (zk.re + zm.re);
-            v.im = T(0.5) * (zk.im - zm.im);
-        } else {
-            v.re = T(0.5) * (zk.im + zm.im);
-            v.im = T(-0.5) * (zk.re - zm.re);
-        }
-    }
-    return v;
-}
+struct alignas(16) vec4 {
+    T v[4];
+};
 
-template <typename T>
-__global__ void __launch_bounds__(512) k_plane_fwd(int nin, int logn,
-                                                   const T *__restrict__ M,
-                                                   cplx<T> *__restrict__ spec,
-                                                   const cplx<T> *__restrict__ tw_g,
-                                                   int P, double *__restrict__ qr2_partial,
-                                                   int cw, int cws, int cpb, int nzs) {
+template <typename T, int N, bool HALF>
+__global__ void __launch_bounds__(128) k_plane_fwd(const T *__restrict__ M,
+                                                   cplx<T> *__restrict__ spec, int P, int pb,
+                                                   int nblk, int nzl, int nzs,
+                                                   double *__restrict__ qr2_partial) {
+    constexpr int nin = HALF ? N / 2 : N, npair = nin / 2, nh = N / 2 + 1, LS = N + 1;
+    constexpr int NV = nin * nin / 4, LB = 8;
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int nf = 1 << logn, nh = nf / 2 + 1, npair = nin / 2, ls = lds_line(nf);
-    const int z = blockIdx.x;
-    const int btid = threadIdx.x, bnthr = blockDim.x;
-    {
-        // system blockIdx.z of a batch: meshes at fixed strides
-        const int64_t sy = blockIdx.z, K = (int64_t)nin * nin * nin;
-        M += sy * (P + 1) * K;
-        spec += sy * P * nzs * nf * nh;
-        if (qr2_partial != nullptr) qr2_partial += sy * nin;
-    }
-    if ((int)blockIdx.y == (P + cpb - 1) / cpb) {
-        // blocks of the extra row: sum over plane z of the per-cell q|u|^2
-        // (component P of M), fixed-order reduction
-        __shared__ double red[8];
-        const T *pl = M + ((int64_t)P * nin + z) * nin * nin;
-        double acc = 0.0;
-        for (int idx = btid; idx < nin * nin; idx += bnthr) acc += (double)pl[idx];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        if ((btid & 63) == 0) red[btid >> 6] = acc;
-        __syncthreads();
-        if (btid == 0) {
-            double t = 0.0;
-            for (int w = 0; w < (bnthr >> 6); ++w) t += red[w];
-            qr2_partial[z] = t;
-        }
-        return;
-    }
-    // cpb components per block, one group of blockDim.x / cpb threads each
-    // with its own LDS lines (a group past the last component repeats it and
-    // stores nothing); tid, nthr below are the group's
-    const int nthr = bnthr / cpb, grp = btid / nthr, tid = btid - grp * nthr;
-    const bool live = (int)blockIdx.y * cpb + grp < P;
-    const int c = live ? (int)blockIdx.y * cpb + grp : P - 1;
-    cplx<T> *tw = (cplx<T> *)lds_raw;      // shared by the groups (each writes all of it)
-    cplx<T> *buf1 = tw + nf / 2 + grp * (npair * ls + nf * cws);   // [npair][ls] row pairs
-    cplx<T> *buf2 = buf1 + npair * ls;     // [nf][cws]: kx columns k0 .. k0 + cw - 1
-    // twiddle load in flight together with the plane's loads (nf/2 <= blockDim.x)
-    const cplx<T> twv = tw_g[tid < nf / 2 ? tid : 0];
-    const T *plane = M + ((int64_t)c * nin + z) * nin * nin;
-    // rows are paired (2j, 2j+1) into one complex row; loads are issued in
-    // batches of kLoadBatch before their LDS stores
-    for (int base = tid; base < npair * nf; base += nthr * kLoadBatch) {
-        cplx<T> v[kLoadBatch];
-#pragma unroll
-        for (int u = 0; u < kLoadBatch; ++u) {
-            const int idx = base + u * nthr;
-            const int j = idx >> logn, x = idx & (nf - 1);
-            v[u] = {T(0), T(0)};
-            if (idx < npair * nf && x < nin) {
-                v[u].re = plane[(2 * j) * nin + x];
-                v[u].im = plane[(2 * j + 1) * nin + x];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kLoadBatch; ++u) {
-            const int idx = base + u * nthr;
-            if (idx < npair * nf) buf1[(idx >> logn) * ls + (idx & (nf - 1))] = v[u];
-        }
-    }
-    asm volatile("" ::"v"(twv.re), "v"(twv.im));   // keeps the load above this point
-    if (tid < nf / 2) tw[tid] = twv;
-    __syncthreads();
-    fft_lines<T, false>(buf1, logn, npair, ls, 1, tw, tid, nthr);
-    cplx<T> *out = spec + ((int64_t)c * nzs + z) * nf * nh;
-    // y FFTs: all nh kx columns at once, or in chunks of cw when LDS is short
-    if (cw >= nh) {
-        for (int idx = tid; idx < nf * nh; idx += nthr) {
-            const int y = idx / nh, k = idx - y * nh;
-            buf2[idx] = unpack_row_pair(buf1, ls, nf, nin, y, k);
-        }
-        __syncthreads();
-        fft_lines<T, false>(buf2, logn, nh, 1, nh, tw, tid, nthr);
-        if (live)
-            for (int idx = tid; idx < nf * nh; idx += nthr) out[idx] = buf2[idx];
-        return;
-    }
-    for (int k0 = 0; k0 < nh; k0 += cw) {
-        const int cn = nh - k0 < cw ? nh - k0 : cw;
-        for (int idx = tid; idx < nf * cn; idx += nthr) {
-            const int y = idx / cn, kk = idx - y * cn;
-            buf2[y * cws + kk] = unpack_row_pair(buf1, ls, nf, nin, y, k0 + kk);
-        }
-        __syncthreads();
-        fft_lines<T, false>(buf2, logn, cn, 1, cws, tw, tid, nthr);
-        for (int idx = tid; live && idx < nf * cn; idx += nthr) {
-            const int y = idx / cn, kk = idx - y * cn;
-            out[y * nh + k0 + kk] = buf2[y * cws + kk];
-        }
-        __syncthreads();   // buf2 is refilled by the next chunk
-    }
-}
-
-template <typename T>
-__global__ void __launch_bounds__(512) k_plane_inv(int nout, int logn,
-                                                   const cplx<T> *__restrict__ spec,
-                                                   T *__restrict__ L,
-                                                   const cplx<T> *__restrict__ tw_g, T scale,
-                                                   int P, int cw, int cws, int cpb, int nzs) {
+    cplx<T> *xb = (cplx<T> *)lds_raw;            // [pb][npair][LS]
+    const int tid = threadIdx.x, nthr = blockDim.x;
     {
         // system blockIdx.z of a batch: meshes at fixed strides
         const int64_t sy = blockIdx.z;
-        const int nf_ = 1 << logn;
-        spec += sy * P * nzs * nf_ * (nf_ / 2 + 1);
+        M += sy * (P + 1) * nin * nin * nin;
+        spec += sy * P * nzs * N * nh;
+        if (qr2_partial != nullptr) qr2_partial += sy * nin;
+    }
+    if ((int)blockIdx.x >= nblk) {
+        // periodic: sum over plane z of the per-cell q|u|^2 (component P of
+        // M), fixed-order reduction
+        __shared__ double red[2];
+        const int z = blockIdx.x - nblk;
+        const T *pl = M + ((int64_t)P * nin + z) * nin * nin;
+        double acc = 0.0;
+        for (int idx = tid; idx < nin * nin; idx += nthr) acc += (double)pl[idx];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        if ((tid & 63) == 0) red[tid >> 6] = acc;
+        __syncthreads();
+        if (tid == 0) qr2_partial[z] = nthr > 64 ? red[0] + red[1] : red[0];
+        return;
+    }
+    const int first = blockIdx.x * pb, left = P * nzl - first, cnt = left < pb ? left : pb;
+    // loads of a batch are issued before their LDS stores
+    for (int base = tid; base < cnt * NV; base += nthr * LB) {
+        vec4<T> v[LB];
+#pragma unroll
+        for (int u = 0; u < LB; ++u) {
+            const int idx = base + u * nthr < cnt * NV ? base + u * nthr : cnt * NV - 1;
+            const int q = first + idx / NV, c = q / nzl;
+            v[u] = ((const vec4<T> *)(M + ((int64_t)c * nin + (q - c * nzl)) * nin * nin))[idx % NV];
+        }
+#pragma unroll
+        for (int u = 0; u < LB; ++u) {
+            const int idx = base + u * nthr;
+            if (idx < cnt * NV) {
+                const int y = idx % NV / (nin / 4), x = idx % (nin / 4) * 4;
+                T *d = (T *)(xb + (idx / NV * npair + (y >> 1)) * LS + x) + (y & 1);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) d[2 * k] = v[u].v[k];
+            }
+        }
+    }
+    __syncthreads();
+    for (int line = tid; line < cnt * npair; line += nthr) {
+        cplx<T> *b = xb + line * LS;
+        cplx<T> w[N];
+        static_for<0, N>([&](auto ix) {
+            constexpr int x = decltype(ix)::value;
+            if constexpr (x < nin) w[x] = b[x];
+            else w[x] = {T(0), T(0)};
+        });
+        fft_reg<N, false, T>(w);
+        static_for<0, N>([&](auto ix) { b[decltype(ix)::value] = w[decltype(ix)::value]; });
+    }
+    __syncthreads();
+    for (int it = tid; it < cnt * nh; it += nthr) {
+        const int pl = it / nh, k = it - pl * nh, km = (N - k) & (N - 1);
+        const cplx<T> *b = xb + pl * npair * LS;
+        cplx<T> w[N];
+        static_for<0, N / 2>([&](auto ij) {
+            constexpr int j = decltype(ij)::value;
+            if constexpr (j < npair) {
+                const cplx<T> zk = b[j * LS + k], zm = b[j * LS + km];
+                w[2 * j] = {T(0.5) * (zk.re + zm.re), T(0.5) * (zk.im - zm.im)};
+                w[2 * j + 1] = {T(0.5) * (zk.im + zm.im), T(-0.5) * (zk.re - zm.re)};
+            } else {
+                w[2 * j] = {T(0), T(0)};
+                w[2 * j + 1] = {T(0), T(0)};
+            }
+        });
+        fft_reg<N, false, T>(w);
+        const int q = first + pl, c = q / nzl;
+        cplx<T> *out = spec + ((int64_t)c * nzs + (q - c * nzl)) * N * nh + k;
+        static_for<0, N>([&](auto iy) { out[decltype(iy)::value * nh] = w[decltype(iy)::value]; });
+    }
+}
+
+template <typename T, int N, bool HALF>
+__global__ void __launch_bounds__(128) k_plane_inv(const cplx<T> *__restrict__ spec,
+                                                   T *__restrict__ L, T scale, int P, int pb,
+                                                   int nzl, int nzs) {
+    constexpr int nout = HALF ? N / 2 : N, npair = nout / 2, nh = N / 2 + 1, LS = N + 1;
+    constexpr int NV = nout * nout / 4;
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    cplx<T> *xb = (cplx<T> *)lds_raw;            // [pb][npair][LS]
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    {
+        // system blockIdx.z of a batch: meshes at fixed strides
+        const int64_t sy = blockIdx.z;
+        spec += sy * P * nzs * N * nh;
         L += sy * P * nout * nout * nout;
     }
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    const int nf = 1 << logn, nh = nf / 2 + 1, npair = nout / 2, ls = lds_line(nf);
-    const int z = blockIdx.x;
-    // cpb components per block as in k_plane_fwd; tid, nthr are the group's
-    const int nthr = blockDim.x / cpb, grp = threadIdx.x / nthr, tid = threadIdx.x - grp * nthr;
-    const bool live = (int)blockIdx.y * cpb + grp < P;
-    const int c = live ? (int)blockIdx.y * cpb + grp : P - 1;
-    cplx<T> *tw = (cplx<T> *)lds_raw;      // shared by the groups (each writes all of it)
-    cplx<T> *buf2 = tw + nf / 2 + grp * (nf * cws + npair * ls);   // [nf][cws]: kx columns k0 .. k0 + cw - 1
-    cplx<T> *buf1 = buf2 + nf * cws;       // [npair][ls]
-    // twiddle load in flight together with the spectrum's (nf/2 <= blockDim.x)
-    const cplx<T> twv = tw_g[tid < nf / 2 ? tid : 0];
-    const cplx<T> *in = spec + ((int64_t)c * nzs + z) * nf * nh;
-    // y inverse FFTs: all nh kx columns at once, or in chunks of cw when LDS
-    // is short; the results are packed into the C2R rows of buf1 (columns kx
-    // and nf - kx of a row pair come from column kx)
-    const int nchunk = cw >= nh ? 1 : (nh + cw - 1) / cw;
-    const int cwl = cw >= nh ? nh : cw;
-    for (int ch = 0; ch < nchunk; ++ch) {
-        const int k0 = ch * cwl;
-        const int cn = nh - k0 < cwl ? nh - k0 : cwl;
-        const int ld = nchunk == 1 ? nh : cws;       // row stride of buf2
-        for (int base = tid; base < nf * cn; base += nthr * kLoadBatch) {
-            cplx<T> v[kLoadBatch];
-#pragma unroll
-            for (int u = 0; u < kLoadBatch; ++u) {
-                // clamped, unconditional loads: the whole batch is issued at once
-                const int idx = base + u * nthr < nf * cn ? base + u * nthr : nf * cn - 1;
-                v[u] = in[nchunk == 1 ? idx : (idx / cn) * nh + k0 + idx % cn];
-            }
-#pragma unroll
-            for (int u = 0; u < kLoadBatch; ++u) asm volatile("" ::"v"(v[u].re), "v"(v[u].im));
-#pragma unroll
-            for (int u = 0; u < kLoadBatch; ++u) {
-                const int idx = base + u * nthr;
-                if (idx < nf * cn) buf2[nchunk == 1 ? idx : (idx / cn) * ld + idx % cn] = v[u];
-            }
-        }
-        if (ch == 0) {
-            asm volatile("" ::"v"(twv.re), "v"(twv.im));
-            if (tid < nf / 2) tw[tid] = twv;
-        }
-        __syncthreads();
-        fft_lines<T, true>(buf2, logn, cn, 1, ld, tw, tid, nthr);
-        if (nchunk == 1) {
-            for (int idx = tid; idx < npair * nf; idx += nthr) {
-                const int j = idx >> logn, k = idx & (nf - 1);
-                const int kk = k <= nf / 2 ? k : nf - k;
-                cplx<T> A = buf2[(2 * j) * nh + kk];
-                cplx<T> B = buf2[(2 * j + 1) * nh + kk];
-                if (k > nf / 2) {
-                    A.im = -A.im;
-                    B.im = -B.im;
-                }
-                buf1[j * ls + k] = {A.re - B.im, A.im + B.re};
-            }
-        } else {
-            for (int idx = tid; idx < npair * cn; idx += nthr) {
-                const int j = idx / cn, kk = idx - j * cn, k = k0 + kk;
-                const cplx<T> A = buf2[(2 * j) * ld + kk];
-                const cplx<T> B = buf2[(2 * j + 1) * ld + kk];
-                buf1[j * ls + k] = {A.re - B.im, A.im + B.re};
-                if (k >= 1 && k < nf / 2) buf1[j * ls + nf - k] = {A.re + B.im, B.re - A.im};
-            }
-        }
-        __syncthreads();   // buf1 complete / buf2 refilled by the next chunk
+    const int first = blockIdx.x * pb, left = P * nzl - first, cnt = left < pb ? left : pb;
+    for (int it = tid; it < cnt * nh; it += nthr) {
+        const int pl = it / nh, k = it - pl * nh;
+        const int q = first + pl, c = q / nzl;
+        const cplx<T> *in = spec + ((int64_t)c * nzs + (q - c * nzl)) * N * nh + k;
+        cplx<T> w[N];
+        static_for<0, N>([&](auto iy) { w[decltype(iy)::value] = in[decltype(iy)::value * nh]; });
+        fft_reg<N, true, T>(w);
+        // C2R row pairs: Z_j[k] = A[k] + i B[k] and, 0 < k < N/2,
+        // Z_j[N - k] = conj(A[k]) + i conj(B[k]) from rows A = 2j, B = 2j + 1
+        cplx<T> *b = xb + pl * npair * LS;
+        static_for<0, npair>([&](auto ij) {
+            constexpr int j = decltype(ij)::value;
+            const cplx<T> A = w[2 * j], B = w[2 * j + 1];
+            b[j * LS + k] = {A.re - B.im, A.im + B.re};
+            if (k > 0 && k < N / 2) b[j * LS + N - k] = {A.re + B.im, B.re - A.im};
+        });
     }
-    fft_lines<T, true>(buf1, logn, npair, ls, 1, tw, tid, nthr);
-    T *plane = L + ((int64_t)c * nout + z) * nout * nout;
-    for (int idx = tid; live && idx < nout * nout; idx += nthr) {
-        const int y = idx / nout, x = idx - y * nout;
-        const cplx<T> v = buf1[(y >> 1) * ls + x];
-        plane[idx] = ((y & 1) ? v.im : v.re) * scale;
+    __syncthreads();
+    for (int line = tid; line < cnt * npair; line += nthr) {
+        cplx<T> *b = xb + line * LS;
+        cplx<T> w[N];
+        static_for<0, N>([&](auto ix) { w[decltype(ix)::value] = b[decltype(ix)::value]; });
+        fft_reg<N, true, T>(w);
+        static_for<0, nout>([&](auto ix) {
+            constexpr int x = decltype(ix)::value;
+            b[x] = {w[x].re * scale, w[x].im * scale};
+        });
+    }
+    __syncthreads();
+    for (int idx = tid; idx < cnt * NV; idx += nthr) {
+        const int y = idx % NV / (nout / 4), x = idx % (nout / 4) * 4;
+        const T *d = (const T *)(xb + (idx / NV * npair + (y >> 1)) * LS + x) + (y & 1);
+        vec4<T> v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v.v[k] = d[2 * k];
+        const int q = first + idx / NV, c = q / nzl;
+        ((vec4<T> *)(L + ((int64_t)c * nout + (q - c * nzl)) * nout * nout))[idx % NV] = v;
     }
 }
 
@@ -497,71 +444,53 @@ static hipError_t plane_n_launch(const FFTArgs &a, int stage, hipStream_t s) {
 }
 
 // --------------------------------------------------------------- launcher
-static int ilog2(int v) {
-    int l = 0;
-    while ((1 << l) < v) ++l;
-    return l;
-}
-
-template <typename Kern>
-static hipError_t ensure_lds(Kern k, size_t bytes) {
-    if (bytes <= 65536) return hipSuccess;
-    return set_max_lds((const void *)k, bytes);
-}
-
 // Column stage, one instantiation per order in the pmmm_column_*.hip units.
 template <int PO, typename T>
 hipError_t column_launch(const FFTArgs &a, hipStream_t s);
 
-// Shape of a plane block: 256 threads in cpb groups, one component each.
-// Small planes keep only a few lanes busy per FFT stage, so when there are
-// planes enough to fill the GPU (at least 1024 of them) a block takes 8
-// components up to 16 points, 4 at 32, 2 at 64; a launch with fewer planes is
-// latency-bound and keeps one component per block (shorter chains).  The y
-// pass of a 128-point plane runs in chunks of 16 kx columns (row stride 17
-// against bank conflicts), so that a block needs 50 KB of LDS instead of
-// 100 KB and three share a CU.
-struct PlaneShape {
-    int threads, cw, cws, cpb;
-    size_t lds;
-};
-static PlaneShape plane_shape(int n, int nz, int nf, int P, int nsys, size_t csz) {
-    const int nh = nf / 2 + 1;
-    PlaneShape ps;
-    ps.threads = 256;
-    ps.cpb = nf <= 16 ? 8 : (nf == 32 ? 4 : (nf == 64 ? 2 : 1));
-    if ((int64_t)nz * P * nsys < 1024) ps.cpb = 1;
-    ps.cw = nf >= 128 ? 16 : nh;
-    ps.cws = ps.cw == nh ? nh : ps.cw + 1;
-    ps.lds = (size_t)(nf / 2 + ps.cpb * ((n / 2) * lds_line(nf) + nf * ps.cws)) * csz;
-    return ps;
+// Planes per block of the transforms up to 32 points: the columns of pb planes
+// fill one wave; two from 1024 such blocks on, which leave fewer lanes idle
+// (7 x 17 of 128 against 3 x 17 of 64 at 32 points) and still fill the chip.
+static int planes_per(int N, int64_t planes) {
+    const int nh = N / 2 + 1;
+    return planes >= (int64_t)1024 * (128 / nh) ? 128 / nh : 64 / nh;
+}
+
+template <typename T, int N, bool HALF>
+static hipError_t plane_launch(const FFTArgs &a, int stage, hipStream_t s) {
+    const int P = nreal(a.p), nsys = a.nsys > 0 ? a.nsys : 1, npair = (HALF ? N / 2 : N) / 2;
+    const int pb = planes_per(N, (int64_t)P * a.nzl * nsys);
+    const int nblk = (P * a.nzl + pb - 1) / pb, threads = pb * (N / 2 + 1) > 64 ? 128 : 64;
+    const size_t lds = (size_t)pb * npair * (N + 1) * sizeof(cplx<T>);
+    if (stage == 0)   // periodic: one more block per plane sums q|u|^2
+        hipLaunchKernelGGL((k_plane_fwd<T, N, HALF>), dim3(nblk + (HALF ? 0 : N), 1, nsys),
+                           dim3(threads), lds, s, (const T *)a.M, (cplx<T> *)a.spec, P, pb, nblk,
+                           a.nzl, a.nzs, HALF ? nullptr : a.qr2_partial);
+    else
+        hipLaunchKernelGGL((k_plane_inv<T, N, HALF>), dim3(nblk, 1, nsys), dim3(threads), lds, s,
+                           (const cplx<T> *)a.spec, (T *)a.L, T(1.0 / ((double)N * N * a.nfz)), P, pb,
+                           a.nzl, a.nzs);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t plane_dispatch(const FFTArgs &a, int stage, hipStream_t s) {
+    switch (a.nf) {
+        case 4: return a.open ? hipErrorInvalidValue : plane_launch<T, 4, false>(a, stage, s);
+        case 8: return a.open ? plane_launch<T, 8, true>(a, stage, s) : plane_launch<T, 8, false>(a, stage, s);
+        case 16: return a.open ? plane_launch<T, 16, true>(a, stage, s) : plane_launch<T, 16, false>(a, stage, s);
+        case 32: return a.open ? plane_launch<T, 32, true>(a, stage, s) : plane_launch<T, 32, false>(a, stage, s);
+        case 64: return plane_n_launch<T, 64>(a, stage, s);
+        case 128:
+            if constexpr (sizeof(T) == 4) return plane_n_launch<T, 128>(a, stage, s);
+            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <typename T>
 hipError_t launch_conv_stage(const FFTArgs &a, int stage, hipStream_t s) {
     if (a.generic) return launch_generic_stage<T>(a, stage, s);
-    const int P = nreal(a.p);
-    const int nf = a.nf, logn = ilog2(nf), n = a.n;
-    const int nsys = a.nsys > 0 ? a.nsys : 1;
-    const size_t csz = sizeof(cplx<T>);
-    const PlaneShape ps = plane_shape(n, a.nzl, nf, P, nsys, csz);
-    const size_t lds_plane = ps.lds;
-    hipError_t e = hipSuccess;
-    if (stage != 1 && (nf == 64 || nf == 128)) {
-        if (sizeof(T) == 8 && nf == 128) return hipErrorInvalidValue;
-        return nf == 64 ? plane_n_launch<T, 64>(a, stage, s) : plane_n_launch<T, 128>(a, stage, s);
-    }
-    if (stage == 0) {
-        e = ensure_lds(k_plane_fwd<T>, lds_plane);
-        if (e != hipSuccess) return e;
-        // periodic: one extra row of blocks sums q|u|^2 per plane
-        const int crows = (P + ps.cpb - 1) / ps.cpb;
-        const int rows = a.open ? crows : crows + 1;
-        hipLaunchKernelGGL(k_plane_fwd<T>, dim3(a.nzl, rows, nsys), dim3(ps.threads), lds_plane, s, n,
-                           logn, (const T *)a.M, (cplx<T> *)a.spec, (const cplx<T> *)a.tw, P,
-                           a.open ? nullptr : a.qr2_partial, ps.cw, ps.cws, ps.cpb, a.nzs);
-        return hipGetLastError();
-    }
     if (stage == 1) {
         switch (a.p) {
             case 0: return column_launch<0, T>(a, s);
@@ -578,13 +507,7 @@ hipError_t launch_conv_stage(const FFTArgs &a, int stage, hipStream_t s) {
             default: return hipErrorInvalidValue;
         }
     }
-    e = ensure_lds(k_plane_inv<T>, lds_plane);
-    if (e != hipSuccess) return e;
-    const T scale = T(1.0 / ((double)nf * nf * a.nfz));
-    hipLaunchKernelGGL(k_plane_inv<T>, dim3(a.nzl, (P + ps.cpb - 1) / ps.cpb, nsys), dim3(ps.threads),
-                       lds_plane, s, n, logn, (const cplx<T> *)a.spec, (T *)a.L,
-                       (const cplx<T> *)a.tw, scale, P, ps.cw, ps.cws, ps.cpb, a.nzs);
-    return hipGetLastError();
+    return plane_dispatch<T>(a, stage, s);
 }
 
 template hipError_t launch_conv_stage<float>(const FFTArgs &, int, hipStream_t);
