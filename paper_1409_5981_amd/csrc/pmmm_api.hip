@@ -73,7 +73,7 @@ struct Plan {
     // particle buffers
     int64_t cap = 0, last_n = -1;
     int *cell_of = nullptr, *slot = nullptr, *perm = nullptr, *scell = nullptr, *pos = nullptr;
-    int *lists = nullptr;       // near field: work lists
+    int *lists = nullptr;       // near field: tile list
     int *count = nullptr, *tile_sums = nullptr;  // radix-sort histograms and scan scratch
     void *sorted = nullptr, *staged = nullptr;   // staged: out4<T>[cap] sorted-order results
     int4 *items = nullptr;                       // dense P2M items [dense_items_cap(cap, K)]
@@ -665,6 +665,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
         a.sorted = pb.sorted;
         a.inv_h = pl->inv_h;
         a.lists = pb.lists;
+        a.pieces = pb.slot;   // free after the binning
         a.small = pl->small;
         a.staged = pb.staged;
         PMMM_HIP(launch_near<T>(a, s));

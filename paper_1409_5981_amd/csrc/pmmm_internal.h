@@ -609,7 +609,7 @@ hipError_t launch_bin(const BinArgs &a, hipStream_t s);
 // Partition tiles: 1024 R elements, R = 1, 2 or 4 growing with the particle
 // count.
 constexpr int bin_tile_items(int64_t max_np) {
-    return max_np >= (int64_t(1) << 21) ? 4 : (max_np >= (int64_t(1) << 20) ? 2 : 1);
+    return max_np >= (int64_t(1) << 21) ? 4 : (max_np >= (int64_t(1) << 19) ? 2 : 1);
 }
 constexpr int64_t bin_tiles(int64_t max_np) {
     return max_np > 0 ? (max_np + 1024 * bin_tile_items(max_np) - 1) /
@@ -643,15 +643,24 @@ constexpr int bin_high_bits(int64_t max_np, int64_t K) {
 // Histogram ints per system for every particle count up to max_np (the tile
 // count is not monotonic where R steps up, hence the maximum): the partition's
 // [buckets][tiles] and the bucket starts, then the low-bit histograms of the
-// chunks of large buckets (one of c > kLocalTile particles makes less than
-// 2 c / kLocalTile).
+// chunks of large buckets (one of c > kLocalTile particles makes at most
+// 2 c / kLocalTile; while the partition's bits still grow with the count, the
+// chunks times 2^(low bits) stay below the cells).  At least 512 ints per tile
+// of 1024 (2^20 on 2048, 2^21 on 4096) particles: the work space that
+// pmmm_workspace_bytes reports for them.
 constexpr int64_t bin_hist_ints(int64_t max_np, int64_t K) {
-    const int bits = bin_key_bits(K);
-    const int hb = bits > 19 ? kRadixMaxBits : (bits < 9 ? bits : 9);
+    const int64_t m20 = bin_min64(max_np, (int64_t(1) << 20) - 1), m21 = bin_min64(max_np, (int64_t(1) << 21) - 1);
+    const int64_t least = 512 * bin_max64(1, bin_max64((max_np + 4095) / 4096,
+                                                       bin_max64((m21 + 2047) / 2048, (m20 + 1023) / 1024)));
+    if (max_np == 0) return least;
+    const int bits = bin_key_bits(K), hb = bin_high_bits(max_np, K);
     const int64_t tiles = bin_max64(bin_tiles(max_np),
                                     bin_max64(bin_tiles(bin_min64(max_np, (int64_t(1) << 21) - 1)),
-                                              bin_tiles(bin_min64(max_np, (int64_t(1) << 20) - 1))));
-    return (((tiles + 1) << hb) + ((2 * max_np / kLocalTile + 1) << kLocalMaxBits) + 63) / 64 * 64;
+                                              bin_tiles(bin_min64(max_np, (int64_t(1) << 19) - 1))));
+    const int64_t chunks = max_np > kLocalTile ? 2 * max_np / kLocalTile : 0;
+    const int64_t low = bin_max64(bin_min64(int64_t(1) << bits, chunks << (bits - bin_high_bits(kLocalTile + 1, K))),
+                                  chunks << (bits - hb));
+    return bin_max64(least, (((tiles + 1) << hb) + (bits > 9 ? low : 0) + 63) / 64 * 64);
 }
 constexpr int64_t bin_scan_tiles(int64_t max_np, int64_t K) {
     return (bin_hist_ints(max_np, K) + 4095) / 4096;
@@ -791,13 +800,14 @@ struct NearArgs {
     const int *start, *scell;
     const void *sorted;
     double inv_h;
-    int *lists;                     // [near_list_ints(n, ncell)] work lists
+    int *lists;                     // [near_list_ints(n, ncell)] tiles
+    int *pieces;                    // [n] pieces (the binning's slots, free by then)
     int *small;                     // [5..7]: counts of the lists, zeroed by the binning
     void *staged;                   // out4<T>[n] sorted-order results
 };
 template <typename T>
 hipError_t launch_near(const NearArgs &a, hipStream_t s);
-// Ints of the near field's work lists for n particles on ncell^3 cells.
+// Ints of the near field's tile list for n particles on ncell^3 cells.
 int64_t near_list_ints(int64_t n, int ncell);
 // p[0 .. count) = 0 with a fill kernel.
 hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s);

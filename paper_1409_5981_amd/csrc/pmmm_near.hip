@@ -42,20 +42,20 @@ __host__ __device__ inline bool near_pairs_reach(int64_t np, int n, int cutoff, 
     return w * w * w * np * np >= pairs * n * n;
 }
 
-// Lists of one call: int2 {row, first slot} per tile, int2 {cell, piece} per
-// piece (one-wave pieces from the front of the array, the others from its
-// end), and their counts (zeroed by the binning).  One wave per row of cells
+// Lists of one call: the first slot of every tile, and per piece j of a cell
+// its first slot + j (j is below the cell's count, so the slot names the cell;
+// one-wave pieces from the front of the array, the others from its end), and their counts (zeroed by the binning).  One wave per row of cells
 // (n <= 128: two cells per lane), 16 rows per block, which reserves its places
 // with one atomic per list (one per row took 190 us at 128^2 rows).
 __global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
                                                     const int *__restrict__ start,
-                                                    int2 *__restrict__ tiles,
-                                                    int2 *__restrict__ pieces, int last_piece,
+                                                    int *__restrict__ tiles,
+                                                    int *__restrict__ pieces, int last_piece,
                                                     int *__restrict__ counts) {
     __shared__ int cnt[3][16];          // tiles, light pieces, heavy pieces of each wave
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int r = blockIdx.x * 16 + wid;
-    int row0 = 0, np = 0, c[2] = {0, 0};
+    int row0 = 0, np = 0, c[2] = {0, 0}, first[2] = {0, 0};
     if (r < n * n) {
         const int *row = start + (int64_t)r * n;
         row0 = row[0];
@@ -63,7 +63,8 @@ __global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int x = lane + 64 * u;
-            c[u] = x < n ? row[x + 1] - row[x] : 0;
+            first[u] = x < n ? row[x] : 0;
+            c[u] = x < n ? row[x + 1] - first[u] : 0;
         }
     }
     const bool dense = near_pairs_reach(np, n, cutoff, kNearLight);
@@ -97,12 +98,12 @@ __global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
     }
     __syncthreads();
     for (int t = lane; t < nt; t += 64)
-        tiles[cnt[0][wid] + t] = make_int2(r, row0 + t * kNearTile);
+        tiles[cnt[0][wid] + t] = row0 + t * kNearTile;
     int at = cnt[heavy ? 2 : 1][wid] + inc - J[0] - J[1];
 #pragma unroll
     for (int u = 0; u < 2; ++u)
         for (int j = 0; j < J[u]; ++j, ++at)
-            pieces[heavy ? last_piece - at : at] = make_int2(r * n + lane + 64 * u, j);
+            pieces[heavy ? last_piece - at : at] = first[u] + j;
 }
 
 // 1 / sqrt(r2).  FP64: the hardware estimate and one third-order step, to
@@ -146,7 +147,7 @@ __global__ void __launch_bounds__(kNearTile) k_near(int n, int logn, int cutoff,
                                                     const int *__restrict__ start,
                                                     const int *__restrict__ scell,
                                                     const particle4<T> *__restrict__ sorted,
-                                                    const int2 *__restrict__ tiles,
+                                                    const int *__restrict__ tiles,
                                                     const int *__restrict__ ntiles, T inv_h,
                                                     out4<T> *__restrict__ staged, int accumulate) {
     __shared__ NearSrc<T> src[kNearTile];
@@ -155,7 +156,7 @@ __global__ void __launch_bounds__(kNearTile) k_near(int n, int logn, int cutoff,
     const int t = blockIdx.x;
     if (t >= ntiles[0]) return;  // the whole (one-wave) block leaves
     const RowIdx<POW2> ri{n, logn};
-    const int r = tiles[t].x, s0 = tiles[t].y;
+    const int s0 = tiles[t], r = ri.div(scell[s0]);
     const int s1 = min(s0 + kNearTile, start[ri.mul(r + 1)]);
     const int s = s0 + lane;
     const bool live = s < s1;
@@ -293,7 +294,7 @@ template <typename T, bool POW2, int NT>
 __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 6 : 4) k_near_cells(
     int n, int logn, int cutoff, int periodic, const int *__restrict__ start,
     const int *__restrict__ scell, const particle4<T> *__restrict__ sorted,
-    const int2 *__restrict__ pieces, int stride, const int *__restrict__ npieces, T inv_h,
+    const int *__restrict__ pieces, int stride, const int *__restrict__ npieces, T inv_h,
     out4<T> *__restrict__ staged, int accumulate) {
     constexpr int kMaxRows = 25, U = 2, kChunk = U * NT;   // sources staged at a time
     __shared__ __align__(16) union {
@@ -309,14 +310,14 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 6 : 4) k_near_cells(
     const RowIdx<POW2> ri{n, logn};
     const int np = npieces[0];
     for (int it = blockIdx.x; it < np; it += gridDim.x) {
-        const int2 pc = pieces[(int64_t)it * stride];
-        const int cell = pc.x, r = ri.div(cell), tx = ri.mod(cell);
+        const int pc = pieces[(int64_t)it * stride];
+        const int cell = scell[pc], r = ri.div(cell), tx = ri.mod(cell);
         const int iz = ri.div(r), iy = ri.mod(r);
         const int c0 = start[cell], cn = start[cell + 1] - c0;
         // pieces of a cell are as even as possible
         const int J = (cn + kNearTargets - 1) / kNearTargets;
         const int per = (cn + J - 1) / J;
-        const int s0 = c0 + pc.y * per;
+        const int s0 = c0 + (pc - c0) * per;
         const int cnt = min(per, c0 + cn - s0);
         if (cnt <= 0) continue;   // the same for every thread
         if (tid < 64) {
@@ -475,15 +476,14 @@ __global__ void __launch_bounds__(NT, sizeof(T) == 4 ? 6 : 4) k_near_cells(
     }
 }
 
-// Upper bounds of the lists for np particles on n^3 cells (a non-empty cell of
-// k particles makes at most 1 + k / kNearTargets pieces).
+// Upper bounds of the lists for np particles on n^3 cells (every piece holds a
+// particle).
 static int64_t max_row_tiles(int64_t np, int n) { return (np + kNearTile - 1) / kNearTile + (int64_t)n * n; }
-static int64_t max_pieces(int64_t np) { return np + np / kNearTargets; }
 
 template <typename T, bool POW2>
 static void near_launch(const NearArgs &a, int logn, hipStream_t s) {
-    const int64_t most = max_pieces(a.n);
-    int2 *tiles = (int2 *)a.lists, *pieces = tiles + max_row_tiles(a.n, a.ncell);
+    const int64_t most = a.n;
+    int *tiles = a.lists, *pieces = a.pieces;
     int *counts = a.small + 5;
     const int rows = a.ncell * a.ncell, blocks = (int)(most < 32768 ? most : 32768);
     const particle4<T> *sorted = (const particle4<T> *)a.sorted;
@@ -528,7 +528,7 @@ hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s) {
     return hipGetLastError();
 }
 
-int64_t near_list_ints(int64_t n, int ncell) { return 2 * (max_row_tiles(n, ncell) + max_pieces(n)); }
+int64_t near_list_ints(int64_t n, int ncell) { return max_row_tiles(n, ncell); }
 
 template hipError_t launch_near<float>(const NearArgs &, hipStream_t);
 template hipError_t launch_near<double>(const NearArgs &, hipStream_t);
