@@ -37,7 +37,7 @@ if ROOT not in sys.path:
 METRIC = "particles/s, PMMM far field (P2M+FFT M2L+L2P) at rel. RMS force err <=1e-6"
 HBM_PEAK = 8.0e12            # B/s, MI355X HBM3E
 FP32_PEAK = 157.3e12         # FLOP/s, MI355X FP32 vector
-# FP32 operations of one near-field pair (k_near): the offset (4), r^2 (5),
+# FP32 operations of one near-field pair (k_near_cells): the offset (4), r^2 (5),
 # rsq (1), q/r and the potential sum (2), 1/r^3 (2), three gradient FMAs (6)
 NEAR_FLOPS_PER_PAIR = 20
 FP64_PEAK = 78.6e12
@@ -847,7 +847,7 @@ def bench_hier(args, workload):
     flops = 2 * P * P * pairs
     roof = {"bound": "alu", "achieved": flops / t_fine / 1e12, "peak": FP32_PEAK / 1e12,
             "unit": "TFLOP/s", "frac": flops / t_fine / FP32_PEAK, "traffic": None,
-            "kernel": "fine-level eq. M2L sums (k_hier_m2l_cell)", "kernel_us": t_fine * 1e6,
+            "kernel": "fine-level eq. M2L sums (k_hier_m2l)", "kernel_us": t_fine * 1e6,
             "algorithmic_flops": flops, "fine_pairs": pairs,
             "call_frac": flops / t_med / FP32_PEAK}
     extra = {}

@@ -80,7 +80,8 @@ typedef struct pmmm_hier_s *pmmm_hier;
  *               smallest power-of-two cube n^3 (n >= 4) of the same cells
  *               that holds the box at its corner.  The open convolution is
  *               linear, so the extra cells, which hold no particles, change
- *               no result; they cost FFT and M2L work.  The FFT mesh nf (2n
+ *               no result; they cost FFT and M2L work, less along z, whose
+ *               transform only holds nz cells.  The FFT mesh nf (2n
  *               open, n periodic) may be at most 128 (FP32) or 64 (FP64).
  *   box         edge lengths b of the box [0, b_x) x [0, b_y) x [0, b_z);
  *               cells must be cubic (b_a / n_a equal to 1e-12 relative).
@@ -384,6 +385,8 @@ int pmmm_plan_sync_status(pmmm_plan plan);
  *                    orders and Im G~ for odd orders (the other part vanishes
  *                    by the parity of the kernel); periodic plans carry the
  *                    self term -2 alpha h / sqrt(pi) in component 0.
+ * L and the transfer kernel of an open plan with nz < n come from a plan of the
+ * cube that the copy builds and frees.
  * `bytes` must equal pmmm_plan_mesh_bytes(plan, which). */
 size_t pmmm_plan_mesh_bytes(pmmm_plan plan, int which);
 int pmmm_plan_copy_mesh(pmmm_plan plan, int which, void *host_dst, size_t bytes);
