@@ -260,15 +260,17 @@ __device__ __forceinline__ void fft_reg(cplx<T> *v) {
 
 // In-place FFTs of `nlines` lines of N points in LDS, natural order in and
 // out; element e of line t at buf[t * lstride + e * estride].  tw[k] =
-// exp(-2 pi i k / N), k < N/2, in LDS.  N <= 16: one thread per line in
-// registers.  N = 16 N2 (N2 = 2, 4, 8): four-step scheme, 16-point register
+// exp(-2 pi i k / N), k < N/2, in LDS.  N <= 16 (FP32: 32): one thread per line
+// in registers (against 32 points in two steps, whole calls on periodic 32^3
+// cells: p = 7 151 -> 150 us, p = 8 135 -> 131, p = 10 178 -> 171; open 16^3,
+// p = 9 118 -> 112).  N = 16 N2 (N2 = 2, 4, 8): four-step scheme, 16-point register
 // FFTs over n1 for each t2 (x[n1 N2 + t2]), twiddle W_N^(t2 k1), then N2-point
 // FFTs over t2; X[k1 + 16 k2] ends at position k1 + 16 k2.  nthr must be a
 // multiple of 64.  Ends with a barrier.
 template <typename T, bool INV, int N>
 __device__ void fft_lines_n(cplx<T> *buf, int nlines, int lstride, int estride,
                             const cplx<T> *tw, int tid, int nthr) {
-    if constexpr (N <= 16) {
+    if constexpr (N <= (sizeof(T) == 4 ? 32 : 16)) {
         for (int line = tid; line < nlines; line += nthr) {
             cplx<T> *b = buf + line * lstride;
             cplx<T> v[N];
