@@ -795,6 +795,22 @@ template <typename T>
 hipError_t launch_unpermute(int64_t n, const int *pos, const void *staged, void *phi, void *gx,
                             void *gy, void *gz, int accumulate, hipStream_t s);
 
+// Pairs per cell, (2c+1)^3 times the square of the row's mean occupancy, from
+// which a row goes cell by cell, and from which a piece takes 256 threads.
+// Total calls at p = 3, in us, row tiles / one wave / 256 threads per piece:
+// c = 2, 32^3 cells of 1.2 particles 246 / 285 / -, of 1.8 335 / 175 / 355, of
+// 13 973 / 453 / 551, of 18 - / 698 / 796; c = 1, 64^3 cells of 2.3 423 / 543 / -,
+// of 6 794 / 714 / 1549; 16^3 cells of 49 (64400 pairs) - / 269 / 219.
+// np, a row's particles or on the host all of them, is any 32-bit count: from
+// 2^20 on both answers are yes, and 125 times its square would not fit 64 bits
+// from 2.7e8 on.
+constexpr int64_t kNearLight = 384;
+constexpr int64_t kNearHeavy = 49152;
+__host__ __device__ constexpr bool near_pairs_reach(int64_t np, int n, int cutoff, int64_t pairs) {
+    const int64_t w = 2 * cutoff + 1, m = bin_min64(np, int64_t(1) << 20);
+    return w * w * w * m * m >= pairs * n * n;
+}
+
 struct NearArgs {
     int64_t n;
     int ncell, cutoff, periodic;

@@ -29,19 +29,6 @@ constexpr int kNearTile = 64;       // targets per tile (one wave)
 constexpr int kNearThreads = 256;   // threads per piece of a heavy cell
 constexpr int kNearTargets = 64;    // targets per piece: two per lane, several source parts
 constexpr int kNearSeg = 63;        // sources of one part per chunk (an FP32 running sum)
-// Pairs per cell, (2c+1)^3 times the square of the row's mean occupancy, from
-// which a row goes cell by cell, and from which a piece takes 256 threads.
-// Total calls at p = 3, in us, row tiles / one wave / 256 threads per piece:
-// c = 2, 32^3 cells of 1.2 particles 246 / 285 / -, of 1.8 335 / 175 / 355, of
-// 13 973 / 453 / 551, of 18 - / 698 / 796; c = 1, 64^3 cells of 2.3 423 / 543 / -,
-// of 6 794 / 714 / 1549; 16^3 cells of 49 (64400 pairs) - / 269 / 219.
-constexpr int64_t kNearLight = 384;
-constexpr int64_t kNearHeavy = 49152;
-__host__ __device__ inline bool near_pairs_reach(int64_t np, int n, int cutoff, int64_t pairs) {
-    const int64_t w = 2 * cutoff + 1;
-    return w * w * w * np * np >= pairs * n * n;
-}
-
 // Lists of one call: the first slot of every tile, and per piece j of a cell
 // its first slot + j (j is below the cell's count, so the slot names the cell;
 // one-wave pieces from the front of the array, the others from its end), and their counts (zeroed by the binning).  One wave per row of cells

@@ -1,0 +1,53 @@
+"""Host rules of the library's dispatch that no call small enough for a test
+reaches, checked on the CPU: a program that includes the internal header is
+compiled for the host and compares each rule with the same one in wider
+arithmetic (or with the sizes it has to cover)."""
+import os
+import shutil
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1409_5981_amd", "csrc")
+
+
+def _host_program(tmp_path, body):
+    """Output of a host program with `body` in main."""
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include <cstdio>\n#include "pmmm_internal.h"\nusing namespace pmmm;\n'
+                   "int main() {\n" + body + "\nreturn 0;\n}\n")
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    r = subprocess.run([hipcc, "-std=c++17", "-x", "hip", "--offload-host-only", "-I", CSRC,
+                        str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, (r.stdout, r.stderr)
+    return r.stdout
+
+
+def test_near_rule_holds_for_every_particle_count(tmp_path):
+    """near_pairs_reach, which chooses the near field's kernels on the host and
+    the kind of a row on the GPU, is (2c+1)^3 np^2 >= pairs n^2 for every count
+    up to 2^31 - 1: around its switch, at powers of two and in steps between."""
+    out = _host_program(tmp_path, """
+    long long bad = 0, seen = 0, first = -1;
+    for (int c = 1; c <= 2; ++c)
+        for (int n = 3; n <= 128; ++n)
+            for (int64_t pairs : {kNearLight, kNearHeavy}) {
+                auto check = [&](int64_t np) {
+                    if (np < 0 || np > INT32_MAX) return;
+                    const __int128 w = 2 * c + 1;
+                    const bool want = w * w * w * np * np >= (__int128)pairs * n * n;
+                    ++seen;
+                    if (near_pairs_reach(np, n, c, pairs) != want) {
+                        if (bad == 0) first = np;
+                        ++bad;
+                    }
+                };
+                for (int64_t np = 0; np < 20000; ++np) check(np);
+                for (int e = 0; e < 32; ++e)
+                    for (int64_t d = -2; d <= 2; ++d) check((int64_t(1) << e) + d);
+                for (int64_t np = 1000003; np <= INT32_MAX; np += 9999991) check(np);
+            }
+    printf("%lld %lld %lld\\n", bad, seen, first);""")
+    bad, seen, first = (int(v) for v in out.split())
+    assert seen > 10 ** 7 and bad == 0, (bad, first)
