@@ -77,7 +77,7 @@ struct Plan {
     int *count = nullptr, *tile_sums = nullptr;  // radix-sort histograms and scan scratch
     void *sorted = nullptr, *staged = nullptr;   // staged: out4<T>[cap] sorted-order results
     int4 *items = nullptr;                       // dense P2M items [dense_items_cap(cap, K)]
-    float *partial = nullptr;                    // [dense_slots_cap(cap)][P + 1]
+    void *partial = nullptr;                     // T[dense_slots_cap(cap)][P + 1]
     hipStream_t last_stream = nullptr;
     // multi-charge workspace (chunks of up to kMultiMaxSets sets)
     int mcap_sets = 0;
@@ -280,7 +280,7 @@ static size_t particle_bytes(const Plan *pl, int64_t n) {
            sizeof(int) * (size_t)(near_list_ints(n, pl->n) + bin_hist_ints(n, pl->K) +
                                   bin_scan_tiles(n, pl->K)) +
            sizeof(int4) * (size_t)dense_items_cap(n, pl->K) +
-           sizeof(float) * (size_t)dense_slots_cap(n) * (pl->P + 1);
+           pl->tsize * (size_t)dense_slots_cap(n) * (pl->P + 1);
 }
 
 static void free_particles(Plan *pl) {
@@ -323,7 +323,7 @@ static int ensure_capacity(Plan *pl, int64_t n) {
     PMMM_HIP(hipMalloc(&pl->count, sizeof(int) * bin_hist_ints(n, pl->K)));
     PMMM_HIP(hipMalloc(&pl->tile_sums, sizeof(int) * bin_scan_tiles(n, pl->K)));
     PMMM_HIP(hipMalloc(&pl->items, sizeof(int4) * dense_items_cap(n, pl->K)));
-    PMMM_HIP(hipMalloc(&pl->partial, sizeof(float) * dense_slots_cap(n) * (pl->P + 1)));
+    PMMM_HIP(hipMalloc(&pl->partial, pl->tsize * dense_slots_cap(n) * (pl->P + 1)));
     pl->cap = n;
     return PMMM_OK;
 }
@@ -441,7 +441,7 @@ struct PBuf {
     int *cell_of, *slot, *perm, *scell, *pos, *lists, *count, *tile_sums;
     void *sorted, *staged;
     int4 *items;
-    float *partial;
+    void *partial;
     int64_t items_cap, slots_cap;
 };
 
@@ -761,8 +761,8 @@ static int far_noalloc(pmmm_plan_s *pl, int64_t n, const float *x, const float *
     pb.count = (int *)(b + 5 * kNoAllocInts + 2 * kNoAllocRecs);
     pb.tile_sums = (int *)(b + 5 * kNoAllocInts + 2 * kNoAllocRecs + kNoAllocHist);
     pb.items = (int4 *)(b + 5 * kNoAllocInts + 2 * kNoAllocRecs + kNoAllocHist + kNoAllocSums);
-    pb.partial = (float *)(b + 5 * kNoAllocInts + 2 * kNoAllocRecs + kNoAllocHist +
-                           kNoAllocSums + kNoAllocItems);
+    pb.partial = b + 5 * kNoAllocInts + 2 * kNoAllocRecs + kNoAllocHist + kNoAllocSums +
+                 kNoAllocItems;
     pb.items_cap = kNoAllocItemsCap;
     pb.slots_cap = kNoAllocSlotsCap;
     pb.lists = nullptr;  // far field only

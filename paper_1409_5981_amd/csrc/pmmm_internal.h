@@ -727,7 +727,7 @@ struct P2MArgs {
     int whole;                      // they are whole cells
     int64_t items_cap;
     const int *small;
-    float *partial;                 // [nsys][slots_cap][P + 1] sums of the items of split cells
+    void *partial;                  // T[nsys][slots_cap][P + 1] sums of the items of split cells
     int64_t slots_cap;
     const void *sorted;
     void *M;                        // [P + 1][K]: moments, then sum q |u|^2

@@ -82,7 +82,7 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
                                              const particle4<T> *__restrict__ sorted,
                                              int dense_thr, const int4 *__restrict__ items,
                                              int64_t items_cap, const int *__restrict__ small,
-                                             float *__restrict__ partial, int64_t slots_cap,
+                                             T *__restrict__ partial, int64_t slots_cap,
                                              T *__restrict__ M, int order,
                                              const int64_t *__restrict__ prange) {
     constexpr int P = nreal(PO);
@@ -139,7 +139,7 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
                     if (c < NV) {
                         if (J == 1) M[(int64_t)c * K + moment_place(cell, order)] = acc[64 * g];
                         else if (ps + j < slots_cap)
-                            partial[(int64_t)(ps + j) * NV + c] = (float)acc[64 * g];
+                            partial[(int64_t)(ps + j) * NV + c] = acc[64 * g];
                     }
                 }
             }
@@ -195,7 +195,7 @@ template <typename T>
 __global__ void __launch_bounds__(256) k_p2m_combine(int K, int NV, const int4 *__restrict__ items,
                                                      int64_t items_cap,
                                                      const int *__restrict__ small,
-                                                     const float *__restrict__ partial,
+                                                     const T *__restrict__ partial,
                                                      int64_t slots_cap, T *__restrict__ M,
                                                      int order) {
     __shared__ double red[4][nreal(PMMM_PMAX) + 1];
@@ -215,15 +215,15 @@ __global__ void __launch_bounds__(256) k_p2m_combine(int K, int NV, const int4 *
         const int cell = e.x, J = e.y, ps = e.z;
         const bool ok = ps >= 0 && ps + J <= slots_cap;
         for (int c = lane; c < NV; c += 64) {
-            const float *pc = partial + (int64_t)ps * NV + c;
+            const T *pc = partial + (int64_t)ps * NV + c;
             double acc[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) acc[u] = 0.0;
             for (int k0 = wid; ok && k0 < J; k0 += 32) {
-                float v[8];
+                T v[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    v[u] = k0 + 4 * u < J ? pc[(int64_t)(k0 + 4 * u) * NV] : 0.0f;
+                    v[u] = k0 + 4 * u < J ? pc[(int64_t)(k0 + 4 * u) * NV] : T(0);
 #pragma unroll
                 for (int u = 0; u < 8; ++u) acc[u] += (double)v[u];
             }
@@ -391,7 +391,7 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
 #define PMMM_P2M_W(GG, W)                                                                        \
     hipLaunchKernelGGL((k_p2m<PO, T, GG, W>), dim3(nlight + dense, nsys), dim3(256), 0, s, K,    \
                        nlight, st, so, a.dense_threshold, a.items, a.items_cap, a.small,         \
-                       a.partial, a.slots_cap, M, a.order, a.prange)
+                       (T *)a.partial, a.slots_cap, M, a.order, a.prange)
 #define PMMM_P2M_G(GG)                                                                           \
     case GG:                                                                                     \
         if (a.whole) PMMM_P2M_W(GG, true);                                                       \
@@ -413,8 +413,8 @@ static hipError_t p2m_dispatch_g(const P2MArgs &a, hipStream_t s) {
         const int64_t nsplit = dense_splits_cap_of(a.slots_cap);
         const int cblocks = (int)(nsplit < 2048 ? nsplit : 2048);
         hipLaunchKernelGGL(k_p2m_combine<T>, dim3(cblocks, nsys), dim3(256),
-                           0, s, K, nreal(PO) + 1, a.items, a.items_cap, a.small, a.partial,
-                           a.slots_cap, M, a.order);
+                           0, s, K, nreal(PO) + 1, a.items, a.items_cap, a.small,
+                           (const T *)a.partial, a.slots_cap, M, a.order);
     }
     return hipGetLastError();
 }

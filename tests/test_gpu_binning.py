@@ -66,3 +66,16 @@ def test_binning_batch_of_small_systems():
             ref = opm.far_field(s.pos, s.q.astype(np.float64), oracle_cfg(s))
             assert_parity({"phi": got[0], "grad": np.stack(got[1:], 1)}, ref.phi, ref.grad, "f32",
                           f"batch system of {s.n}")
+
+
+@pytest.mark.parametrize("n,n_cells,p,boundary,share", [
+    (40000, 8, 2, "open", 0.5), (100000, 8, 8, "periodic", 0.3), (70000, 5, 4, "periodic", 0.0)])
+def test_fp64_cells_of_several_items(n, n_cells, p, boundary, share):
+    """FP64 plans above the whole-cell size: the partial sums of a cell cut
+    into items (one of 20000 or 30000 particles, or every cell of 560) hold 64
+    bits too, so the field keeps the FP64 bounds."""
+    ps = _clustered(n, n_cells, boundary, share, 90 + p, np.float64, 1.0 / 32)
+    ps.p = p
+    res, _ = gpu_far(ps, precision="f64")
+    ref = opm.far_field(ps.pos, ps.q, oracle_cfg(ps))
+    assert_parity(res, ref.phi, ref.grad, "f64", f"split cells {n} on {n_cells}^3 {boundary} p={p}")
