@@ -69,10 +69,10 @@ def test_binning_batch_of_small_systems():
 
 
 @pytest.mark.parametrize("n,n_cells,p,boundary,share", [
-    (40000, 8, 2, "open", 0.5), (100000, 8, 8, "periodic", 0.3), (70000, 5, 4, "periodic", 0.0)])
+    (40000, 8, 2, "open", 0.5), (100000, 8, 8, "periodic", 0.3), (140000, 5, 4, "periodic", 0.0)])
 def test_fp64_cells_of_several_items(n, n_cells, p, boundary, share):
     """FP64 plans above the whole-cell size: the partial sums of a cell cut
-    into items (one of 20000 or 30000 particles, or every cell of 560) hold 64
+    into items (one of 20000 or 30000 particles, or every cell of about 1100) hold 64
     bits too, so the field keeps the FP64 bounds."""
     ps = _clustered(n, n_cells, boundary, share, 90 + p, np.float64, 1.0 / 32)
     ps.p = p
