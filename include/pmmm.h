@@ -140,8 +140,9 @@ int pmmm_far_f32(pmmm_plan plan, int64_t n, const float *x, const float *y, cons
  * as pmmm_far_f32 for an FP32 (or BF16X3) plan, but the per-particle work
  * space (cell indices, permutation, sorted records, sorted-order results)
  * lives in a static device array of the library sized for
- * PMMM_NOALLOC_MAX_N particles (52 bytes each, 13 MiB; each GPU the library
- * runs on holds its own copy until the process ends), so the call makes no
+ * PMMM_NOALLOC_MAX_N particles on any mesh (52 bytes each and the sort's and
+ * P2M's tables, 16 MiB in all; each GPU the library runs on holds its own copy
+ * until the process ends), so the call makes no
  * allocation and records no events (stage profiling does not apply).  The
  * array's device address is looked up when a plan is created on a device.
  * n above PMMM_NOALLOC_MAX_N returns PMMM_EINVAL before anything is

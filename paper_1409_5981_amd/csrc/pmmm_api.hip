@@ -686,8 +686,9 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
 constexpr int64_t kNoAllocMaxN = PMMM_NOALLOC_MAX_N;
 constexpr size_t kNoAllocInts = (size_t)kNoAllocMaxN * sizeof(int);
 constexpr size_t kNoAllocRecs = (size_t)kNoAllocMaxN * sizeof(particle4<float>);
-// radix-sort histograms (512 buckets per tile) and their scan scratch
-constexpr int64_t kNoAllocMaxK = int64_t(1) << 18;   // cells of an FP32 plan at most
+// sort histograms and their scan scratch, for the mesh that needs most: the
+// largest, a periodic one of 128^3 cells, whose partition has 2048 buckets
+constexpr int64_t kNoAllocMaxK = int64_t(1) << 21;
 constexpr size_t kNoAllocHist = (size_t)bin_hist_ints(kNoAllocMaxN, kNoAllocMaxK) * sizeof(int);
 constexpr size_t kNoAllocSums =
     ((size_t)bin_scan_tiles(kNoAllocMaxN, kNoAllocMaxK) * sizeof(int) + 255) / 256 * 256;

@@ -63,3 +63,18 @@ def test_noalloc_refuses_oversize_and_fp64():
     with pytest.raises((PMMMError, ValueError)):
         f64.far_noalloc(*d, out=tuple(torch.empty(4, dtype=torch.float64, device="cuda")
                                       for _ in range(4)))
+
+
+@pytest.mark.parametrize("n_cells,n", [(128, 1 << 18), (128, 77826), (64, 1 << 18)])
+def test_noalloc_takes_large_meshes(n_cells, n):
+    """The static scratch holds the sort tables of every mesh a plan accepts,
+    the periodic ones of 64^3 and 128^3 cells included."""
+    import torch
+    from paper_1409_5981_amd._lib import Plan
+    plan = Plan(n_cells, 1, "periodic")
+    t = _particles(n, 90)
+    out = tuple(torch.empty(n, dtype=torch.float32, device="cuda") for _ in range(4))
+    got = _np(plan.far_noalloc(*t, out=out))
+    plan.sync_status()
+    ref = _np(plan.far(*t))
+    assert_parity(got, ref["phi"], ref["grad"], "f32", f"noalloc periodic {n_cells}^3 N={n}")
