@@ -23,8 +23,9 @@
 //                 work items of the cells above the dense threshold
 //   k_bin_keys, k_bin_small   all of it in two launches, for few particles and
 //                 cells
-// Cell index: I = floor(r n / b) per axis, clamped to [0, n-1]; periodic
-// positions are first wrapped into the box (in cell units).
+// Cell index: I = floor(r n / b) per axis, clamped to [0, n-1], along z of a
+// flat open box to the box's own top cell (the stages of a call stop there);
+// periodic positions are first wrapped into the box (in cell units).
 //
 // Batches: blockIdx.y selects one of several independent systems on meshes of
 // the same size; prange[2s], prange[2s+1] bound system s's particles in the
@@ -40,8 +41,8 @@ constexpr int kLocalBuckets = 1 << kLocalMaxBits;   // k_rb_hist2, k_rb_local
 constexpr int kScanOneBlock = 16384;   // histograms up to this size: one-block scan
 
 template <typename T>
-__device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int lim, int periodic, int &ic,
-                                           T &u, int &outside) {
+__device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int top, int lim,
+                                           int periodic, int &ic, T &u, int &outside) {
     T s = v * inv_h;
     if (periodic) {
         s = s - T(n) * floor(s / T(n));
@@ -49,7 +50,7 @@ __device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int lim, int per
         outside = 1;
     }
     int i = (int)floor(s);
-    i = i < 0 ? 0 : (i > n - 1 ? n - 1 : i);
+    i = i < 0 ? 0 : (i > top - 1 ? top - 1 : i);
     ic = i;
     u = s - T(i) - T(0.5);
 }
@@ -87,12 +88,12 @@ __global__ void __launch_bounds__(256) k_bin_empty(int K, int *__restrict__ star
 template <typename T>
 __device__ __forceinline__ int cell_record(const T *__restrict__ x, const T *__restrict__ y,
                                            const T *__restrict__ z, const T *__restrict__ q,
-                                           int64_t i, T inv_h, int nc, int periodic,
+                                           int64_t i, T inv_h, int nc, int topz, int periodic,
                                            particle4<T> &rec) {
     int ix, iy, iz, out = 0;
-    cell_coord(x[i], inv_h, nc, nc, periodic, ix, rec.ux, out);
-    cell_coord(y[i], inv_h, nc, nc, periodic, iy, rec.uy, out);
-    cell_coord(z[i], inv_h, nc, nc, periodic, iz, rec.uz, out);
+    cell_coord(x[i], inv_h, nc, nc, nc, periodic, ix, rec.ux, out);
+    cell_coord(y[i], inv_h, nc, nc, nc, periodic, iy, rec.uy, out);
+    cell_coord(z[i], inv_h, nc, topz, nc, periodic, iz, rec.uz, out);
     rec.q = q != nullptr ? q[i] : T(0);
     return (iz * nc + iy) * nc + ix;
 }
@@ -139,9 +140,9 @@ __global__ void __launch_bounds__(1024) k_rb_hist(
         const int64_t j = (int64_t)t * (1024 * R) + r * 1024 + threadIdx.x;
         int ix, iy, iz;
         T u;
-        cell_coord(xv[r], inv_h, nc, lim.x, periodic, ix, u, out);
-        cell_coord(yv[r], inv_h, nc, lim.y, periodic, iy, u, out);
-        cell_coord(zv[r], inv_h, nc, lim.z, periodic, iz, u, out);
+        cell_coord(xv[r], inv_h, nc, nc, lim.x, periodic, ix, u, out);
+        cell_coord(yv[r], inv_h, nc, nc, lim.y, periodic, iy, u, out);
+        cell_coord(zv[r], inv_h, nc, lim.z, lim.z, periodic, iz, u, out);
         kv[r] = j < np ? (iz * nc + iy) * nc + ix : -1;
     }
     if (out && np > 0) {
@@ -295,7 +296,7 @@ template <typename T, int R>
 __global__ void __launch_bounds__(1024) k_rb_scatter(
     const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
     const T *__restrict__ y, const T *__restrict__ z, const T *__restrict__ q, T inv_h, int nc,
-    int periodic, int *__restrict__ keys_out, int *__restrict__ vals_out,
+    int topz, int periodic, int *__restrict__ keys_out, int *__restrict__ vals_out,
     particle4<T> *__restrict__ recs_out, const int *__restrict__ offs, int64_t hist_ints,
     int tiles, int shift, int bits, int K, int *__restrict__ pos, int *__restrict__ start,
     int dense_thr, int whole, int4 *__restrict__ items, int64_t items_cap, int64_t splits_cap,
@@ -336,7 +337,7 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
         const int e = wid * 64 * R + r * 64 + lane;
         const int64_t i = p0 + t0 + (e < na ? e : 0);
         if (e < na) {
-            key[r] = cell_record(x, y, z, q, i, inv_h, nc, periodic, rec[r]);
+            key[r] = cell_record(x, y, z, q, i, inv_h, nc, topz, periodic, rec[r]);
             val[r] = (int)i;
         } else {
             key[r] = 0;
@@ -738,9 +739,9 @@ __global__ void __launch_bounds__(256) k_bin_keys(
     if (j >= np) return;
     int ix, iy, iz, out = 0;
     T u;
-    cell_coord(x[p0 + j], inv_h, nc, lim.x, periodic, ix, u, out);
-    cell_coord(y[p0 + j], inv_h, nc, lim.y, periodic, iy, u, out);
-    cell_coord(z[p0 + j], inv_h, nc, lim.z, periodic, iz, u, out);
+    cell_coord(x[p0 + j], inv_h, nc, nc, lim.x, periodic, ix, u, out);
+    cell_coord(y[p0 + j], inv_h, nc, nc, lim.y, periodic, iy, u, out);
+    cell_coord(z[p0 + j], inv_h, nc, lim.z, lim.z, periodic, iz, u, out);
     if (out) *flag = 1;
     keys[p0 + j] = (iz * nc + iy) * nc + ix;
 }
@@ -749,7 +750,7 @@ template <typename T>
 __global__ void __launch_bounds__(1024) k_bin_small(
     const int64_t *__restrict__ prange, int64_t n, const T *__restrict__ x,
     const T *__restrict__ y, const T *__restrict__ z, const T *__restrict__ q, T inv_h, int nc,
-    int periodic, int K, int bits, const int *__restrict__ keys, int *__restrict__ keys_out,
+    int topz, int periodic, int K, int bits, const int *__restrict__ keys, int *__restrict__ keys_out,
     int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out, int *__restrict__ pos,
     int *__restrict__ start, int dense_thr, int whole, int4 *__restrict__ items,
     int64_t items_cap, int64_t splits_cap, int *__restrict__ small) {
@@ -767,7 +768,7 @@ __global__ void __launch_bounds__(1024) k_bin_small(
     const bool act = tid < kSmallTile && t0 + tid < np;
     particle4<T> rec{T(0), T(0), T(0), T(0)};
     int key = 0, slot = 0;
-    if (act) key = cell_record(x, y, z, q, i, inv_h, nc, periodic, rec);
+    if (act) key = cell_record(x, y, z, q, i, inv_h, nc, topz, periodic, rec);
     for (int d = tid; d < 2 * nb; d += 1024) cur[d] = 0;
     __syncthreads();
     constexpr int U = 8;
@@ -868,7 +869,7 @@ static hipError_t radix_bin(const BinArgs &a, int K, int64_t maxn, hipStream_t s
     const bool one = lb == 0;           // the buckets are the cells
     hipLaunchKernelGGL((k_rb_scatter<T, R>), dim3(tiles, nsys), dim3(1024), lds, s, a.prange, a.n,
                        (const T *)a.x, (const T *)a.y, (const T *)a.z, (const T *)a.q, inv_h,
-                       a.ncell, a.periodic, one ? a.scell : a.cell_of, one ? a.perm : a.slot,
+                       a.ncell, lim.z, a.periodic, one ? a.scell : a.cell_of, one ? a.perm : a.slot,
                        one ? (particle4<T> *)a.sorted : recs, a.count, hist_ints, tiles, lb, hb, K,
                        one ? a.pos : nullptr, one ? a.start : nullptr, a.dense_threshold, a.whole,
                        a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
@@ -910,7 +911,7 @@ hipError_t launch_bin(const BinArgs &a, hipStream_t s) {
         hipLaunchKernelGGL(k_bin_small<T>, dim3(blocks, nsys), dim3(1024),
                            (size_t)2 * sizeof(int) << bits, s, a.prange, a.n, (const T *)a.x,
                            (const T *)a.y, (const T *)a.z, (const T *)a.q, T(a.inv_h), a.ncell,
-                           a.periodic, K, bits, a.cell_of, a.scell, a.perm,
+                           lim.z, a.periodic, K, bits, a.cell_of, a.scell, a.perm,
                            (particle4<T> *)a.sorted, a.pos, a.start, a.dense_threshold, a.whole,
                            a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
         return hipGetLastError();

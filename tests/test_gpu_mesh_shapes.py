@@ -246,3 +246,31 @@ def test_open_flat_box_tunings_and_meshes(dims, p):
     res = {"phi": out[0].double().cpu().numpy(),
            "grad": torch.stack(list(out[1:]), 1).double().cpu().numpy()}
     assert_parity(res, ref.phi, ref.grad, "f32", f"flat {dims} autotuned")
+
+
+@pytest.mark.parametrize("dims,n", [((12, 6, 9), 600), ((40, 36, 24), 3000)])
+@pytest.mark.parametrize("above", [0.0, 0.5, 3.5])
+def test_particle_above_a_flat_box(dims, n, above):
+    """A particle on or above the top of a flat open box is flagged and kept
+    in the box's top cell, as at the border of a cubic one: all results are
+    finite (device memory held NaN before the plan was made), and on the top
+    face they are those of the particle just below it."""
+    import torch
+    from paper_1409_5981_amd._lib import PMMM_EDOMAIN
+    junk = torch.full((1 << 28,), float("nan"), device="cuda")
+    del junk
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    pos, q, box = _set(dims, n, 21, np.float32)
+    h = box / dims[0]
+    pos[17, 2] = np.float32((dims[2] + above) * h)
+    for mode in ("far", "total"):
+        res, _, st = _gpu(pos, q, dims, 4, box, "f32", 2, mode=mode)
+        assert st == PMMM_EDOMAIN
+        assert np.isfinite(res["phi"]).all() and np.isfinite(res["grad"]).all()
+        if above == 0.0:
+            inside = pos.copy()
+            inside[17, 2] = np.nextafter(pos[17, 2], np.float32(0))
+            ref, _, st = _gpu(inside, q, dims, 4, box, "f32", 2, mode=mode)
+            assert st == 0
+            assert_parity(res, ref["phi"], ref["grad"], "f32", f"top face of {dims} {mode}")
