@@ -16,6 +16,7 @@
 //                 runs (key, caller index, particle record)
 //   k_rb_hist2    histograms of the low bits for the chunks of buckets above
 //                 kLocalTile particles (clustered input; other blocks leave)
+//   k_rb_sums2    running sums of those over the chunks of a bucket of many
 //   k_rb_local    sorts a bucket, or one chunk of a large one, by the low bits
 //                 into its final place: sorted cell, permutation, records and,
 //                 on request, each particle's sorted slot; the bucket's
@@ -39,6 +40,13 @@ namespace pmmm {
 constexpr int kRadixBuckets = 1 << kRadixMaxBits;   // k_rb_hist, k_rb_scatter
 constexpr int kLocalBuckets = 1 << kLocalMaxBits;   // k_rb_hist2, k_rb_local
 constexpr int kScanOneBlock = 16384;   // histograms up to this size: one-block scan
+// A chunk of a bucket of J <= kChunkRows chunks reads the J low-bit histograms
+// itself; of a larger one it finds them summed (k_rb_sums2), where the call has
+// more than kChunkSumMinN particles.  Up to there J is at most 256 and reading
+// all rows costs 10 us with every particle in one bucket, the launch 2-3 us of
+// every call.
+constexpr int kChunkRows = 64;
+constexpr int64_t kChunkSumMinN = int64_t(1) << 20;
 
 template <typename T>
 __device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int top, int lim,
@@ -544,6 +552,89 @@ __global__ void __launch_bounds__(1024) k_rb_hist2(const int64_t *__restrict__ p
     for (int d = tid; d < nl; d += 1024) h[d] = s_hist[d];
 }
 
+// Low-bit histograms of a bucket of more than kChunkRows chunks into inclusive
+// sums over its chunks, so that a chunk reads two rows of them where it would
+// read J (one bucket of 2^22 particles on 64^3 cells: binning 276 -> 168 us, of
+// 2^25 8501 -> 1297).  Blocks take the large buckets in turn, 64 digits
+// each: the 16 waves sum contiguous shares of the rows, then write them from
+// the sum of the shares before.
+constexpr int kSumGroups = 8;           // blocks per 64 digits
+__global__ void __launch_bounds__(1024) k_rb_sums2(const int64_t *__restrict__ prange, int64_t n,
+                                                   int *__restrict__ hist, int64_t hist_ints,
+                                                   int tiles, int nb, int lbits) {
+    constexpr int DP = kRadixBuckets / 1024, U = 16;
+    __shared__ int scr[16], share[16][64], found, large_mbase[kRadixBuckets], large_J[kRadixBuckets];
+    int64_t p0, np;
+    sys_range(prange, n, p0, np);
+    hist += (int64_t)blockIdx.y * hist_ints;
+    const int *first_of = hist + (int64_t)nb * tiles;
+    const int nl = 1 << lbits, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    // rows before each bucket of several chunks (as find_chunk counts them)
+    int J[DP], ms = 0, large = 0;
+#pragma unroll
+    for (int u = 0; u < DP; ++u) {
+        const int d = tid * DP + u;
+        const int cnt = d < nb ? (d + 1 < nb ? first_of[d + 1] : (int)np) - first_of[d] : 0;
+        const int c = (cnt + kLocalTile - 1) / kLocalTile;
+        J[u] = c > 1 ? c : 0;
+        ms += J[u];
+        large |= c > kChunkRows;
+    }
+    if (tid == 0) found = 0;
+    if (!__syncthreads_or(large)) return;
+    int mi = ms;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int m = __shfl_up(mi, off, 64);
+        if (lane >= off) mi += m;
+    }
+    if (lane == 63) scr[wid] = mi;
+    __syncthreads();
+    mi -= ms;
+    for (int w = 0; w < wid; ++w) mi += scr[w];
+#pragma unroll
+    for (int u = 0; u < DP; ++u) {
+        if (J[u] > kChunkRows) {
+            const int at = atomicAdd(&found, 1);   // in any order
+            large_mbase[at] = mi;
+            large_J[at] = J[u];
+        }
+        mi += J[u];
+    }
+    __syncthreads();
+    const int digit = (int)(blockIdx.x / kSumGroups) * 64 + lane;
+    const bool act = digit < nl;
+    for (int b = 0; b < found; ++b) {
+        const int rows = large_J[b], per = (rows + 15) / 16;
+        if (large_mbase[b] % kSumGroups != (int)(blockIdx.x % kSumGroups)) continue;
+        int *h = hist + (int64_t)nb * (tiles + 1) + (int64_t)large_mbase[b] * nl + digit;
+        const int r0 = min(wid * per, rows), r1 = min(r0 + per, rows);
+        int sum = 0;
+        for (int k0 = r0; k0 < r1; k0 += U) {
+            int v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) v[k] = act && k0 + k < r1 ? h[(int64_t)(k0 + k) * nl] : 0;
+#pragma unroll
+            for (int k = 0; k < U; ++k) sum += v[k];
+        }
+        __syncthreads();                // the previous bucket's shares have been read
+        share[wid][lane] = sum;
+        __syncthreads();
+        int run = 0;
+        for (int w = 0; w < wid; ++w) run += share[w][lane];
+        for (int k0 = r0; k0 < r1; k0 += U) {
+            int v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) v[k] = act && k0 + k < r1 ? h[(int64_t)(k0 + k) * nl] : 0;
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                run += v[k];
+                if (act && k0 + k < r1) h[(int64_t)(k0 + k) * nl] = run;
+            }
+        }
+    }
+}
+
 // LDS of the local sort: the per-wave counts [16][nl], later the staging area
 // of the chunk (its records are the largest array).
 template <typename T>
@@ -564,7 +655,7 @@ __global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) k_rb_local(
     const int *__restrict__ vals_in, const particle4<T> *__restrict__ recs_in,
     int *__restrict__ keys_out, int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out,
     int *__restrict__ pos, int *__restrict__ start, const int *__restrict__ hist,
-    int64_t hist_ints, int tiles, int nb, int lbits, int dense_thr, int whole,
+    int64_t hist_ints, int tiles, int nb, int lbits, int summed, int dense_thr, int whole,
     int4 *__restrict__ items,
     int64_t items_cap, int64_t splits_cap, int *__restrict__ small) {
     constexpr int RM = kLocalTile / 1024;
@@ -628,12 +719,17 @@ __global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) k_rb_local(
         all = tot;
         if (c.J > 1) {
             const int *h = hist + (int64_t)nb * (tiles + 1) + (int64_t)c.mbase * nl + tid;
-            all = 0;
+            if (c.J > summed) {         // rows hold inclusive sums
+                before = c.j > 0 ? h[(int64_t)(c.j - 1) * nl] : 0;
+                all = h[(int64_t)(c.J - 1) * nl];
+            } else {
+                all = 0;
 #pragma unroll 8
-            for (int j = 0; j < c.J; ++j) {
-                const int v = h[(int64_t)j * nl];
-                before += j < c.j ? v : 0;
-                all += v;
+                for (int j = 0; j < c.J; ++j) {
+                    const int v = h[(int64_t)j * nl];
+                    before += j < c.j ? v : 0;
+                    all += v;
+                }
             }
         }
     }
@@ -879,11 +975,16 @@ static hipError_t radix_bin(const BinArgs &a, int K, int64_t maxn, hipStream_t s
     if (maxn > kLocalTile)
         hipLaunchKernelGGL(k_rb_hist2, dim3(chunks, nsys), dim3(1024), 0, s, a.prange, a.n,
                            a.cell_of, a.count, hist_ints, tiles, nb, lb);
+    const bool sums = maxn > kChunkSumMinN;
+    if (sums)
+        hipLaunchKernelGGL(k_rb_sums2, dim3((((1u << lb) + 63) / 64) * kSumGroups, nsys), dim3(1024), 0,
+                           s, a.prange, a.n, a.count, hist_ints, tiles, nb, lb);
     lds = local_lds<T>(lb);
     if ((e = set_max_lds((const void *)k_rb_local<T>, lds)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_rb_local<T>, dim3(chunks, nsys), dim3(1024), lds, s, a.prange, a.n, K,
                        a.cell_of, a.slot, recs, a.scell, a.perm, (particle4<T> *)a.sorted, a.pos,
-                       a.start, a.count, hist_ints, tiles, nb, lb, a.dense_threshold, a.whole,
+                       a.start, a.count, hist_ints, tiles, nb, lb, sums ? kChunkRows : INT32_MAX,
+                       a.dense_threshold, a.whole,
                        a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
     return hipGetLastError();
 }

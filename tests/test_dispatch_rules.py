@@ -51,3 +51,26 @@ def test_near_rule_holds_for_every_particle_count(tmp_path):
     printf("%lld %lld %lld\\n", bad, seen, first);""")
     bad, seen, first = (int(v) for v in out.split())
     assert seen > 10 ** 7 and bad == 0, (bad, first)
+
+
+def test_sort_scratch_holds_every_smaller_count(tmp_path):
+    """bin_hist_ints of a capacity covers the partition's histograms, the bucket
+    starts and a row of low-bit histograms per chunk (a bucket of c > kLocalTile
+    particles makes at most 2 c / kLocalTile) for every count up to it, and
+    never shrinks."""
+    out = _host_program(tmp_path, """
+    long long bad = 0;
+    for (int n : {3, 4, 5, 8, 9, 16, 24, 32, 40, 64, 128}) {
+        const int64_t K = (int64_t)n * n * n;
+        int64_t prev = 0;
+        for (int64_t np = 1; np < (int64_t(1) << 31); np += np < 10000 ? 1 : np / 1000) {
+            const int hb = bin_high_bits(np, K), lb = bin_key_bits(K) - hb;
+            const int64_t rows = np > kLocalTile ? 2 * np / kLocalTile : 0;
+            const int64_t have = bin_hist_ints(np, K);
+            if ((bin_tiles(np) << hb) + (int64_t(1) << hb) + (lb > 0 ? rows << lb : 0) > have) ++bad;
+            if (have < prev) ++bad;
+            prev = have;
+        }
+    }
+    printf("%lld\\n", bad);""")
+    assert int(out) == 0

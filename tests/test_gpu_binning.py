@@ -79,3 +79,26 @@ def test_fp64_cells_of_several_items(n, n_cells, p, boundary, share):
     res, _ = gpu_far(ps, precision="f64")
     ref = opm.far_field(ps.pos, ps.q, oracle_cfg(ps))
     assert_parity(res, ref.phi, ref.grad, "f64", f"split cells {n} on {n_cells}^3 {boundary} p={p}")
+
+
+# share x n particles in one bucket of the partition (two rows of 32 cells):
+# 33 and 65 chunks, whose histograms every chunk reads itself, 273 to 560, which
+# find them summed, and in FP64 50 and 258.
+@pytest.mark.parametrize("n,share,prec", [
+    (140000, 0.95, "f32"), (290000, 0.91, "f32"), (1200000, 0.93, "f32"), (2400000, 0.955, "f32"),
+    (215000, 0.95, "f64"), (1100000, 0.96, "f64")])
+def test_binning_buckets_of_many_chunks(n, share, prec):
+    dt = np.float32 if prec == "f32" else np.float64
+    rng = np.random.default_rng(n)
+    k = int(n * share)
+    pos = rng.random((n, 3)) * 32
+    pos[:k] = np.array([0, 10, 10]) + rng.random((k, 3)) * np.array([32, 2, 1])
+    pos = (pos[rng.permutation(n)] / 32).astype(dt)
+    pos = np.where(pos >= dt(1), np.nextafter(dt(1), dt(0)), pos)
+    q = (rng.random(n) / n).astype(dt)
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, 32, 2, "periodic")
+    res, plan = gpu_far(ps, precision=prec)
+    ref = opm.far_field(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps))
+    assert_parity(res, ref.phi, ref.grad, prec, f"large bucket {n} {prec}")
+    again, _ = gpu_far(ps, precision=prec, plan=plan)
+    assert all(np.array_equal(res[x], again[x]) for x in res)
