@@ -42,11 +42,11 @@ constexpr int kLocalBuckets = 1 << kLocalMaxBits;   // k_rb_hist2, k_rb_local
 constexpr int kScanOneBlock = 16384;   // histograms up to this size: one-block scan
 // A chunk of a bucket of J <= kChunkRows chunks reads the J low-bit histograms
 // itself; of a larger one it finds them summed (k_rb_sums2), where the call has
-// more than kChunkSumMinN particles.  Up to there J is at most 256 and reading
-// all rows costs 10 us with every particle in one bucket, the launch 2-3 us of
-// every call.
+// more than kChunkSumMinN particles.  Up to there J is at most 512 and reading
+// all rows costs 20 us of 286 with every particle in one bucket (10 of 227 at
+// 2^20), the launch 3 us of every call.
 constexpr int kChunkRows = 64;
-constexpr int64_t kChunkSumMinN = int64_t(1) << 20;
+constexpr int64_t kChunkSumMinN = int64_t(1) << 21;
 
 template <typename T>
 __device__ __forceinline__ void cell_coord(T v, T inv_h, int n, int top, int lim,
@@ -470,10 +470,14 @@ __global__ void __launch_bounds__(1024) k_rb_scatter(
 // start + cnt) and makes J = max(1, ceil(cnt / kLocalTile)) chunks, of which
 // this is chunk j; mbase counts the chunks of the buckets before it that make
 // more than one.  b < 0: no such chunk.  Two barriers; scr: 2 x 16 ints.
+// near: eight chunks in a row go to one XCD (blocks are dealt to the eight in
+// turn), so that the runs which a bucket's chunks write side by side meet in one
+// L2: uniform particles on 64^3 cells, binning of 2^24 665 -> 609 us, of 2^25
+// 1298 -> 1179.  Longer stretches leave XCDs idle where most buckets are empty.
 struct Chunk {
     int b, start, cnt, j, J, mbase;
 };
-__device__ __forceinline__ Chunk find_chunk(int blk, int nb, int64_t np, const int *first_of,
+__device__ __forceinline__ Chunk find_chunk(int blk, int nb, int64_t np, int near, const int *first_of,
                                             int *scr, Chunk *found) {
     constexpr int DP = kRadixBuckets / 1024;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -513,6 +517,11 @@ __device__ __forceinline__ Chunk find_chunk(int blk, int nb, int64_t np, const i
         ji += scr[w];
         mi += scr[16 + w];
     }
+    if (near) {
+        int total = 0;
+        for (int w = 0; w < 16; ++w) total += scr[w];
+        if (blk < (total & ~63)) blk = (blk & ~63) | (blk & 7) << 3 | (blk >> 3 & 7);
+    }
 #pragma unroll
     for (int u = 0; u < DP; ++u) {
         if (blk >= ji && blk < ji + J[u])
@@ -540,7 +549,7 @@ __global__ void __launch_bounds__(1024) k_rb_hist2(const int64_t *__restrict__ p
     for (int d = tid; d < nb; d += 1024)
         large |= (d + 1 < nb ? first_of[d + 1] : (int)np) - first_of[d] > kLocalTile;
     if (!__syncthreads_or(large)) return;
-    const Chunk c = find_chunk(blockIdx.x, nb, np, first_of, scr, &found);
+    const Chunk c = find_chunk(blockIdx.x, nb, np, 0, first_of, scr, &found);
     if (c.b < 0 || c.J == 1) return;    // the same for every thread
     for (int d = tid; d < nl; d += 1024) s_hist[d] = 0;
     __syncthreads();
@@ -554,11 +563,11 @@ __global__ void __launch_bounds__(1024) k_rb_hist2(const int64_t *__restrict__ p
 
 // Low-bit histograms of a bucket of more than kChunkRows chunks into inclusive
 // sums over its chunks, so that a chunk reads two rows of them where it would
-// read J (one bucket of 2^22 particles on 64^3 cells: binning 276 -> 168 us, of
-// 2^25 8501 -> 1297).  Blocks take the large buckets in turn, 64 digits
+// read J (one bucket of 2^22 particles on 64^3 cells: binning 276 -> 164 us, of
+// 2^25 8501 -> 1176).  Blocks take the large buckets in turn, 64 digits
 // each: the 16 waves sum contiguous shares of the rows, then write them from
 // the sum of the shares before.
-constexpr int kSumGroups = 8;           // blocks per 64 digits
+constexpr int kSumGroups = 32;          // blocks per 64 digits
 __global__ void __launch_bounds__(1024) k_rb_sums2(const int64_t *__restrict__ prange, int64_t n,
                                                    int *__restrict__ hist, int64_t hist_ints,
                                                    int tiles, int nb, int lbits) {
@@ -609,9 +618,8 @@ __global__ void __launch_bounds__(1024) k_rb_sums2(const int64_t *__restrict__ p
         if (large_mbase[b] % kSumGroups != (int)(blockIdx.x % kSumGroups)) continue;
         int *h = hist + (int64_t)nb * (tiles + 1) + (int64_t)large_mbase[b] * nl + digit;
         const int r0 = min(wid * per, rows), r1 = min(r0 + per, rows);
-        int sum = 0;
+        int sum = 0, v[U];
         for (int k0 = r0; k0 < r1; k0 += U) {
-            int v[U];
 #pragma unroll
             for (int k = 0; k < U; ++k) v[k] = act && k0 + k < r1 ? h[(int64_t)(k0 + k) * nl] : 0;
 #pragma unroll
@@ -623,9 +631,10 @@ __global__ void __launch_bounds__(1024) k_rb_sums2(const int64_t *__restrict__ p
         int run = 0;
         for (int w = 0; w < wid; ++w) run += share[w][lane];
         for (int k0 = r0; k0 < r1; k0 += U) {
-            int v[U];
+            if (per > U) {              // else the rows are still in v
 #pragma unroll
-            for (int k = 0; k < U; ++k) v[k] = act && k0 + k < r1 ? h[(int64_t)(k0 + k) * nl] : 0;
+                for (int k = 0; k < U; ++k) v[k] = act && k0 + k < r1 ? h[(int64_t)(k0 + k) * nl] : 0;
+            }
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 run += v[k];
@@ -655,7 +664,7 @@ __global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) k_rb_local(
     const int *__restrict__ vals_in, const particle4<T> *__restrict__ recs_in,
     int *__restrict__ keys_out, int *__restrict__ vals_out, particle4<T> *__restrict__ recs_out,
     int *__restrict__ pos, int *__restrict__ start, const int *__restrict__ hist,
-    int64_t hist_ints, int tiles, int nb, int lbits, int summed, int dense_thr, int whole,
+    int64_t hist_ints, int tiles, int nb, int lbits, int summed, int near, int dense_thr, int whole,
     int4 *__restrict__ items,
     int64_t items_cap, int64_t splits_cap, int *__restrict__ small) {
     constexpr int RM = kLocalTile / 1024;
@@ -671,7 +680,7 @@ __global__ void __launch_bounds__(1024, sizeof(T) == 4 ? 8 : 4) k_rb_local(
     hist += (int64_t)blockIdx.y * hist_ints;
     start += (int64_t)blockIdx.y * (K + 1);
     for (int e = tid; e < 16 * nl; e += 1024) wcnt[e] = 0;
-    const Chunk c = find_chunk(blockIdx.x, nb, np, hist + (int64_t)nb * tiles, scr, &found);
+    const Chunk c = find_chunk(blockIdx.x, nb, np, near, hist + (int64_t)nb * tiles, scr, &found);
     if (c.b < 0) return;                // the same for every thread
     const int na = min(c.cnt - c.j * kLocalTile, kLocalTile);
     const int rounds = (na + 1023) >> 10;
@@ -972,6 +981,8 @@ static hipError_t radix_bin(const BinArgs &a, int K, int64_t maxn, hipStream_t s
     if (one) return hipGetLastError();
     // every bucket makes a chunk, and every kLocalTile particles at most one more
     const unsigned chunks = (unsigned)(nb + maxn / kLocalTile);
+    // a bucket makes several chunks on average
+    const int near = maxn > (int64_t)nb * kLocalTile;
     if (maxn > kLocalTile)
         hipLaunchKernelGGL(k_rb_hist2, dim3(chunks, nsys), dim3(1024), 0, s, a.prange, a.n,
                            a.cell_of, a.count, hist_ints, tiles, nb, lb);
@@ -983,9 +994,8 @@ static hipError_t radix_bin(const BinArgs &a, int K, int64_t maxn, hipStream_t s
     if ((e = set_max_lds((const void *)k_rb_local<T>, lds)) != hipSuccess) return e;
     hipLaunchKernelGGL(k_rb_local<T>, dim3(chunks, nsys), dim3(1024), lds, s, a.prange, a.n, K,
                        a.cell_of, a.slot, recs, a.scell, a.perm, (particle4<T> *)a.sorted, a.pos,
-                       a.start, a.count, hist_ints, tiles, nb, lb, sums ? kChunkRows : INT32_MAX,
-                       a.dense_threshold, a.whole,
-                       a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
+                       a.start, a.count, hist_ints, tiles, nb, lb, sums ? kChunkRows : INT32_MAX, near,
+                       a.dense_threshold, a.whole, a.items, a.items_cap, dense_splits_cap_of(a.slots_cap), a.small);
     return hipGetLastError();
 }
 
