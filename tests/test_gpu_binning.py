@@ -81,24 +81,29 @@ def test_fp64_cells_of_several_items(n, n_cells, p, boundary, share):
     assert_parity(res, ref.phi, ref.grad, "f64", f"split cells {n} on {n_cells}^3 {boundary} p={p}")
 
 
-# share x n particles in one bucket of the partition (two rows of 32 cells):
-# 33 and 65 chunks, whose histograms every chunk reads itself, 273 to 560, which
-# find them summed, and in FP64 50 and 258.
-@pytest.mark.parametrize("n,share,prec", [
-    (140000, 0.95, "f32"), (290000, 0.91, "f32"), (1200000, 0.93, "f32"), (2400000, 0.955, "f32"),
-    (215000, 0.95, "f64"), (1100000, 0.96, "f64")])
-def test_binning_buckets_of_many_chunks(n, share, prec):
+# share x n particles in one bucket of the partition, which holds 8 cells of
+# 16^3, 64 of 32^3 and 1024 of 128^3: 33 to 273 chunks (FP64: 50), whose
+# histograms every chunk reads itself, and with more than 2^21 particles 282 to
+# 560, which find them summed.
+@pytest.mark.parametrize("n,n_cells,p,share,prec", [
+    (140000, 32, 2, 0.95, "f32"), (290000, 32, 2, 0.91, "f32"), (1200000, 32, 2, 0.93, "f32"),
+    (2400000, 32, 2, 0.955, "f32"), (2100000, 16, 2, 0.55, "f32"), (2100000, 128, 1, 0.6, "f32"),
+    (215000, 32, 2, 0.95, "f64"), (2100000, 32, 2, 0.9, "f64")])
+def test_binning_buckets_of_many_chunks(n, n_cells, p, share, prec):
+    print(f"large bucket {n} on {n_cells}^3 p={p} {prec}", flush=True)
     dt = np.float32 if prec == "f32" else np.float64
     rng = np.random.default_rng(n)
     k = int(n * share)
-    pos = rng.random((n, 3)) * 32
-    pos[:k] = np.array([0, 10, 10]) + rng.random((k, 3)) * np.array([32, 2, 1])
-    pos = (pos[rng.permutation(n)] / 32).astype(dt)
+    pos = rng.random((n, 3)) * n_cells
+    cells = np.array({16: (8, 1, 1), 32: (32, 2, 1), 128: (128, 8, 1)}[n_cells])
+    pos[:k] = np.array([0, 8, 10]) + rng.random((k, 3)) * cells
+    pos = (pos[rng.permutation(n)] / n_cells).astype(dt)
     pos = np.where(pos >= dt(1), np.nextafter(dt(1), dt(0)), pos)
     q = (rng.random(n) / n).astype(dt)
-    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, 32, 2, "periodic")
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, n_cells, p,
+                            "periodic")
     res, plan = gpu_far(ps, precision=prec)
     ref = opm.far_field(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps))
-    assert_parity(res, ref.phi, ref.grad, prec, f"large bucket {n} {prec}")
+    assert_parity(res, ref.phi, ref.grad, prec, f"large bucket {n} on {n_cells}^3 {prec}")
     again, _ = gpu_far(ps, precision=prec, plan=plan)
     assert all(np.array_equal(res[x], again[x]) for x in res)
