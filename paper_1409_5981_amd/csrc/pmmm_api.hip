@@ -664,6 +664,8 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
         a.scell = pb.scell;
         a.sorted = pb.sorted;
         a.inv_h = pl->inv_h;
+        a.nx = pl->open ? pl->lim[0] : pl->n;
+        a.cells = pl->open ? (int64_t)pl->lim[0] * pl->lim[1] * pl->lim[2] : pl->K;
         a.lists = pb.lists;
         a.pieces = pb.slot;   // free after the binning
         a.small = pl->small;

@@ -795,25 +795,45 @@ template <typename T>
 hipError_t launch_unpermute(int64_t n, const int *pos, const void *staged, void *phi, void *gx,
                             void *gy, void *gz, int accumulate, hipStream_t s);
 
-// Pairs per cell, (2c+1)^3 times the square of the row's mean occupancy, from
-// which a row goes cell by cell, and from which a piece takes 256 threads.
-// Total calls at p = 3, in us, row tiles / one wave / 256 threads per piece:
-// c = 2, 32^3 cells of 1.2 particles 246 / 285 / -, of 1.8 335 / 175 / 355, of
-// 13 973 / 453 / 551, of 18 - / 698 / 796; c = 1, 64^3 cells of 2.3 423 / 543 / -,
-// of 6 794 / 714 / 1549; 16^3 cells of 49 (64400 pairs) - / 269 / 219.
-// np, a row's particles or on the host all of them, is any 32-bit count: from
-// 2^20 on both answers are yes, and 125 times its square would not fit 64 bits
-// from 2.7e8 on.
+// Pairs per cell of a row of cells on average, from its own particles and those
+// of the (2c+1)^2 rows around it, from which it goes cell by cell, and from
+// which a piece takes 256 threads (near_pairs_reach).  Total calls at p = 3, in
+// us, row tiles / one wave / 256 threads per piece: c = 2, 32^3 cells of 1.2
+// particles 246 / 285 / -, of 1.8 335 / 175 / 355, of 13 973 / 453 / 551, of 18
+// - / 698 / 796; c = 1, 64^3 cells of 2.3 423 / 543 / -, of 6 794 / 714 / 1549;
+// 16^3 cells of 49 (64400 pairs) - / 269 / 219.
 constexpr int64_t kNearLight = 384;
 constexpr int64_t kNearHeavy = 49152;
-__host__ __device__ constexpr bool near_pairs_reach(int64_t np, int n, int cutoff, int64_t pairs) {
-    const int64_t w = 2 * cutoff + 1, m = bin_min64(np, int64_t(1) << 20);
-    return w * w * w * m * m >= pairs * n * n;
+// Up to so many cells that can hold a particle, all rows go cell by cell, and up
+// to so many pieces (a cell, or 64 of its targets) all take 256 threads: they
+// run at once then, and a sparse row's tile, which visits the rows around it one
+// after the other, takes longest.  Near calls, tiles and cells by the rows' own
+// pairs, then cells: 164 particles on 5^3 cells, c = 2, half of them in one 96 ->
+// 25 us; 2166 clustered on 10^3, c = 2 294 -> 49; 10637 clustered on 33 x 20 x 3,
+// c = 1 919 -> 227.
+constexpr int64_t kNearFewCells = 4096;
+constexpr int64_t kNearFewPieces = 1536;
+// np particles in the nx cells of a row's box, around in the rows around it (on
+// the host, all particles for both: can any row reach it?).  Any 32-bit counts:
+// from 2^30 on the answer is yes, and the product would not fit 64 bits.
+__host__ __device__ constexpr bool near_pairs_reach(int64_t np, int64_t around, int nx, int cutoff,
+                                                    int64_t pairs) {
+    const int64_t most = int64_t(1) << 30;
+    return (2 * cutoff + 1) * (bin_min64(np, most) * bin_min64(around, most)) >= pairs * nx * nx;
+}
+
+// At most so many rows reach it: each holds pairs nx^2 / ((2c+1) n) of the n
+// particles or more.
+constexpr int64_t near_rows_most(int64_t n, int nx, int cutoff, int64_t pairs) {
+    const int64_t m = bin_min64(n, int64_t(1) << 30);
+    return (2 * cutoff + 1) * (m * m) / (pairs * nx * nx);
 }
 
 struct NearArgs {
     int64_t n;
     int ncell, cutoff, periodic;
+    int nx;                         // cells of a row in the caller's box
+    int64_t cells;                  // cells of the caller's box
     int accumulate;                 // add into staged (a far field already there) or store
     const int *start, *scell;
     const void *sorted;

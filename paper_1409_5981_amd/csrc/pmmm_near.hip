@@ -5,7 +5,7 @@
 //
 // Two kernels share the targets, row of cells (fixed y and z) by row:
 //   k_near_list   lists the work: a row with kNearLight near pairs per cell on
-//                 average gives its non-empty cells, in pieces of at most
+//                 average (near_pairs_reach) gives its non-empty cells, in pieces of at most
 //                 kNearTargets targets; any other row gives tiles of kNearTile
 //                 consecutive sorted targets.  The lists' order
 //                 varies from call to call (positions are reserved with
@@ -34,7 +34,8 @@ constexpr int kNearSeg = 63;        // sources of one part per chunk (an FP32 ru
 // one-wave pieces from the front of the array, the others from its end), and their counts (zeroed by the binning).  One wave per row of cells
 // (n <= 128: two cells per lane), 16 rows per block, which reserves its places
 // with one atomic per list (one per row took 190 us at 128^2 rows).
-__global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
+__global__ void __launch_bounds__(1024) k_near_list(int n, int nx, int cutoff, int periodic,
+                                                    int64_t light_pairs, int64_t heavy_pairs,
                                                     const int *__restrict__ start,
                                                     int *__restrict__ tiles,
                                                     int *__restrict__ pieces, int last_piece,
@@ -42,7 +43,7 @@ __global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
     __shared__ int cnt[3][16];          // tiles, light pieces, heavy pieces of each wave
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int r = blockIdx.x * 16 + wid;
-    int row0 = 0, np = 0, c[2] = {0, 0}, first[2] = {0, 0};
+    int row0 = 0, np = 0, around = 0, c[2] = {0, 0}, first[2] = {0, 0};
     if (r < n * n) {
         const int *row = start + (int64_t)r * n;
         row0 = row[0];
@@ -53,9 +54,20 @@ __global__ void __launch_bounds__(1024) k_near_list(int n, int cutoff,
             first[u] = x < n ? row[x] : 0;
             c[u] = x < n ? row[x + 1] - first[u] : 0;
         }
+        const int w = 2 * cutoff + 1;
+        if (lane < w * w) {             // a row around this one per lane
+            int jz = r / n + lane / w - cutoff, jy = r % n + lane % w - cutoff;
+            const bool in = jz >= 0 && jz < n && jy >= 0 && jy < n;
+            jz += jz < 0 ? n : jz >= n ? -n : 0;
+            jy += jy < 0 ? n : jy >= n ? -n : 0;
+            const int *near = start + ((int64_t)jz * n + jy) * n;
+            if (in || periodic) around = near[n] - near[0];
+        }
     }
-    const bool dense = near_pairs_reach(np, n, cutoff, kNearLight);
-    const bool heavy = near_pairs_reach(np, n, cutoff, kNearHeavy);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) around += __shfl_xor(around, off, 64);
+    const bool dense = near_pairs_reach(np, around, nx, cutoff, light_pairs);
+    const bool heavy = near_pairs_reach(np, around, nx, cutoff, heavy_pairs);
     const int nt = dense ? 0 : (np + kNearTile - 1) / kNearTile;
     int J[2], inc;
 #pragma unroll
@@ -472,23 +484,34 @@ static void near_launch(const NearArgs &a, int logn, hipStream_t s) {
     const int64_t most = a.n;
     int *tiles = a.lists, *pieces = a.pieces;
     int *counts = a.small + 5;
-    const int rows = a.ncell * a.ncell, blocks = (int)(most < 32768 ? most : 32768);
+    const int rows = a.ncell * a.ncell;
     const particle4<T> *sorted = (const particle4<T> *)a.sorted;
-    hipLaunchKernelGGL(k_near_list, dim3((rows + 15) / 16), dim3(1024), 0, s, a.ncell, a.cutoff,
-                       a.start, tiles, pieces, (int)most - 1, counts);
+    const int64_t cells = bin_min64(a.n, a.cells), pieces_most = cells + a.n / kNearTargets;
+    const int64_t heavy = pieces_most <= kNearFewPieces ? 0 : kNearHeavy;
+    const int64_t light = heavy == 0 || cells <= kNearFewCells ? 0 : kNearLight;
+    // blocks loop over the pieces, which may be fewer (with none at all, 32600
+    // blocks of 256 threads take 8.7 us, 3200 2.5)
+    const int64_t most_rows = heavy > 0 ? near_rows_most(a.n, a.nx, a.cutoff, heavy) : rows;
+    const int64_t wide = bin_min64(bin_min64(most_rows, rows) * a.nx + a.n / kNearTargets, pieces_most);
+    const unsigned blocks256 = (unsigned)bin_min64(wide, 32768);
+    const unsigned blocks64 = (unsigned)bin_min64(pieces_most, 32768);
+    hipLaunchKernelGGL(k_near_list, dim3((rows + 15) / 16), dim3(1024), 0, s, a.ncell, a.nx,
+                       a.cutoff, a.periodic, light, heavy, a.start, tiles, pieces, (int)most - 1, counts);
     // launched where the particles suffice for one row of the kind
-    if (near_pairs_reach(a.n, a.ncell, a.cutoff, kNearHeavy))
-        hipLaunchKernelGGL((k_near_cells<T, POW2, kNearThreads>), dim3(blocks), dim3(kNearThreads),
+    if (near_pairs_reach(a.n, a.n, a.nx, a.cutoff, heavy))
+        hipLaunchKernelGGL((k_near_cells<T, POW2, kNearThreads>), dim3(blocks256), dim3(kNearThreads),
                            0, s, a.ncell, logn, a.cutoff, a.periodic, a.start, a.scell, sorted,
                            pieces + most - 1, -1, counts + 2, T(a.inv_h), (out4<T> *)a.staged,
                            a.accumulate);
-    if (near_pairs_reach(a.n, a.ncell, a.cutoff, kNearLight))
-        hipLaunchKernelGGL((k_near_cells<T, POW2, 64>), dim3(blocks), dim3(64), 0, s, a.ncell, logn,
+    if (heavy > 0 && near_pairs_reach(a.n, a.n, a.nx, a.cutoff, light))
+        hipLaunchKernelGGL((k_near_cells<T, POW2, 64>), dim3(blocks64), dim3(64), 0, s, a.ncell, logn,
                            a.cutoff, a.periodic, a.start, a.scell, sorted, pieces, 1, counts + 1,
                            T(a.inv_h), (out4<T> *)a.staged, a.accumulate);
-    hipLaunchKernelGGL((k_near<T, POW2>), dim3((unsigned)max_row_tiles(a.n, a.ncell)),
-                       dim3(kNearTile), 0, s, a.ncell, logn, a.cutoff, a.periodic, a.start, a.scell,
-                       sorted, tiles, counts, T(a.inv_h), (out4<T> *)a.staged, a.accumulate);
+    if (light > 0)
+        hipLaunchKernelGGL((k_near<T, POW2>), dim3((unsigned)max_row_tiles(a.n, a.ncell)),
+                           dim3(kNearTile), 0, s, a.ncell, logn, a.cutoff, a.periodic, a.start,
+                           a.scell, sorted, tiles, counts, T(a.inv_h), (out4<T> *)a.staged,
+                           a.accumulate);
 }
 
 template <typename T>

@@ -26,27 +26,32 @@ def _host_program(tmp_path, body):
 
 def test_near_rule_holds_for_every_particle_count(tmp_path):
     """near_pairs_reach, which chooses the near field's kernels on the host and
-    the kind of a row on the GPU, is (2c+1)^3 np^2 >= pairs n^2 for every count
-    up to 2^31 - 1: around its switch, at powers of two and in steps between."""
+    the kind of a row on the GPU, is (2c+1) np around >= pairs nx^2 for all
+    counts up to 2^31 - 1, and where it holds for a row it holds for the host's
+    question, which has all particles for both counts."""
     out = _host_program(tmp_path, """
     long long bad = 0, seen = 0, first = -1;
+    unsigned long long seed = 1;
+    auto rnd = [&]() { seed = seed * 6364136223846793005ull + 1442695040888963407ull; return seed >> 33; };
     for (int c = 1; c <= 2; ++c)
-        for (int n = 3; n <= 128; ++n)
+        for (int nx = 1; nx <= 128; ++nx)
             for (int64_t pairs : {kNearLight, kNearHeavy}) {
-                auto check = [&](int64_t np) {
-                    if (np < 0 || np > INT32_MAX) return;
-                    const __int128 w = 2 * c + 1;
-                    const bool want = w * w * w * np * np >= (__int128)pairs * n * n;
+                auto check = [&](int64_t np, int64_t around) {
+                    if (np < 0 || around < np || around > INT32_MAX) return;
+                    const bool want = (__int128)(2 * c + 1) * np * around >= (__int128)pairs * nx * nx;
                     ++seen;
-                    if (near_pairs_reach(np, n, c, pairs) != want) {
+                    const bool got = near_pairs_reach(np, around, nx, c, pairs);
+                    if (got != want || (got && !near_pairs_reach(around, around, nx, c, pairs))) {
                         if (bad == 0) first = np;
                         ++bad;
                     }
                 };
-                for (int64_t np = 0; np < 20000; ++np) check(np);
+                for (int64_t np = 0; np < 20000; ++np) check(np, np);
                 for (int e = 0; e < 32; ++e)
-                    for (int64_t d = -2; d <= 2; ++d) check((int64_t(1) << e) + d);
-                for (int64_t np = 1000003; np <= INT32_MAX; np += 9999991) check(np);
+                    for (int k = 0; k < 32; ++k)
+                        for (int64_t d = -1; d <= 1; ++d) check((int64_t(1) << e) + d, (int64_t(1) << k) + d);
+                for (int64_t np = 1000003; np <= INT32_MAX; np += 9999991) check(np, np);
+                for (int k = 0; k < 5000; ++k) check(rnd() >> (rnd() % 31), rnd() >> (rnd() % 31));
             }
     printf("%lld %lld %lld\\n", bad, seen, first);""")
     bad, seen, first = (int(v) for v in out.split())

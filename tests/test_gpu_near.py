@@ -198,3 +198,31 @@ def test_near_coincident_particles(prec, dt, n):
     res, _ = _gpu(ps, prec, "near", cutoff=1)
     inf = np.isinf(res["phi"])
     assert inf[7] and inf[30] and inf.sum() == 2
+
+
+@pytest.mark.parametrize("prec,dt", [("f32", np.float32), ("f64", np.float64)])
+@pytest.mark.parametrize("shape,cutoff,n", [
+    ((9, 4, 4), 2, 900),            # few pieces: 256 threads each
+    ((16, 16, 14), 1, 6000),        # few cells: one wave or 256 threads by the row
+    ((20, 18, 16), 2, 9000)])       # sparse rows far from the crowd in tiles
+def test_near_crowded_cell_in_an_open_box(shape, cutoff, n, prec, dt):
+    """Half the particles in one cell of an open box whose rows are shorter
+    than the mesh's: sparse rows beside the crowd, the crowd, and the rest."""
+    rng = np.random.default_rng(n + cutoff)
+    dims = np.array(shape)
+    pos = rng.random((n, 3)) * dims
+    pos[:n // 2] = dims // 2 + rng.random((n // 2, 3))
+    h = 1.0 / 32
+    pos = (pos[rng.permutation(n)] * h).astype(dt)
+    top = (dims * h).astype(dt)
+    pos = np.where(pos >= top, np.nextafter(top, dt(0)), pos)
+    q = rng.standard_normal(n).astype(dt)
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, shape[0], 3, "open",
+                            box=float(shape[0] * h), shape=shape)
+    from paper_1409_5981_amd._lib import Plan
+    plan = Plan(shape[0], 3, "open", box=ps.box, cutoff=cutoff, precision=prec, shape=shape)
+    res, _ = _gpu(ps, prec, "near", plan=plan)
+    nphi, ng = exact.near(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps, cutoff))
+    assert_parity(res, nphi, ng, prec, f"crowded {shape} c={cutoff} {prec}")
+    again, _ = _gpu(ps, prec, "near", plan=plan)
+    assert all(np.array_equal(res[k], again[k]) for k in res)
