@@ -401,18 +401,28 @@ __global__ __launch_bounds__(64 * kHierMaxSplit, HierMat<PO>::WAVES) void k_hier
 // r; 0 where the lane-per-cell form serves instead:
 //  - matrices above kHierMaxMatBytes (r = 8, or r = 4 with c = 2 at high
 //    orders), which are not kept;
-//  - fewer than 64 coarse cells: lanes of every wave would idle (2^3 cells,
-//    r = 4, p = 4: 452 us against 185);
+//  - coarse meshes so small that much of a neighbourhood lies outside, whose
+//    offsets the matrix form runs for whole waves all the same.  Fine level in
+//    us, table / matrices: 2^3 cells always table (r = 2, c = 1, p = 4 24 / 54);
+//    4^3, c = 2 table below order 8 (r = 2: p = 0 22 / 48, p = 4 147 / 212;
+//    r = 4: p = 0 144 / 350, p = 6 2438 / 3864, p = 8 7797 / 6733); 4^3, c = 1
+//    below order 2 (r = 4: p = 0 67 / 83, p = 1 92 / 98, p = 3 268 / 198); 8^3,
+//    c = 2 below order 2 (r = 2: p = 0 40 / 47, p = 1 52 / 55, p = 2 91 / 78);
+//    larger ones never (8^3, c = 1, r = 2: p = 0 15 / 15, p = 4 67 / 56; 16^3,
+//    c = 2, r = 2: p = 0 78 / 66, p = 4 778 / 382);
+//  - r = 1, where every source is near, up to 16^3 cells (p = 4 7 / 9, p = 5 8 /
+//    10; 32^3: p = 4 14 / 11);
 //  - above order 4, fewer than 1024 waves: a wave's chain of products is then
-//    the longer one (20000 particles, 4^3 cells, r = 2, whole call: p = 8
-//    305 us against 274, p = 10 431 against 404; 8^3, p = 5 195 against 184;
-//    from 1024 waves on 8^3, p = 6 248 against 270, 16^3, p = 8 1271 against
-//    2522; at p = 4 the matrices win down to 4^3 cells, 109 against 121).
+//    the longer one (c = 1, r = 2: 4^3 cells, p = 5 76 / 91, p = 10 263 / 278;
+//    8^3, p = 5 87 / 93; from 1024 waves on 8^3, p = 6 137 / 110, 16^3, p = 8
+//    2353 / 1088).
 template <int PO>
 int64_t hier_mat_floats(int nf, int r, int D) {
     using H = hier_detail::HierMat<PO>;
     const int64_t nc = nf / r, r3 = (int64_t)r * r * r, items = (nc * nc * nc + 63) / 64 * r3;
-    if (nc * nc * nc < 64) return 0;
+    const int c = (D + 1) / r - 1;
+    if (nc < 4 || (nc == 4 && PO < (c == 2 ? 8 : 2)) || (nc == 8 && c == 2 && PO < 2)) return 0;
+    if (r == 1 && nc < 32) return 0;
     if (PO > 4 && items * H::NG * hier_detail::kHierMaxSplit < 1024) return 0;
     const int64_t W = 2 * D + 1, cnt = W * W * W * H::STRIDE;
     return cnt * (int64_t)sizeof(float) <= hier_detail::kHierMaxMatBytes ? cnt : 0;

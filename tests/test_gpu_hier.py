@@ -63,6 +63,18 @@ def test_hier_matrix_form_matches_oracle(n, p, r, c, N):
     assert_parity(res, ref_phi, ref_grad, "f32", f"hier matrices n={n} r={r} c={c} p={p}")
 
 
+# Both sides of the rule that chooses the form by the size of the coarse mesh.
+@pytest.mark.parametrize("n,p,r,c,N", [(4, 1, 2, 1, 900), (4, 2, 2, 1, 900), (4, 4, 2, 2, 900),
+                                       (8, 1, 2, 2, 1500), (8, 2, 2, 2, 1500)])
+def test_hier_forms_by_coarse_mesh(n, p, r, c, N):
+    print(f"hier forms coarse {n}^3 p={p} r={r} c={c} N={N}", flush=True)
+    pos, q = _set(N, 300 * n + p + r)
+    cfg = opm.Config(n=n, p=p, boundary="open", cutoff=c)
+    ref_phi, ref_grad = ohier.far_field(pos.astype(np.float64), q.astype(np.float64), cfg, r)
+    res = _run(n, p, r, c, pos, q)
+    assert_parity(res, ref_phi, ref_grad, "f32", f"hier forms n={n} r={r} c={c} p={p}")
+
+
 def test_hier_total_matches_oracle_and_direct_sum():
     n, p, r, c = 4, 5, 2, 2
     pos, q = _set(5000, 7)
