@@ -36,6 +36,7 @@ constexpr int kNearSeg = 63;        // sources of one part per chunk (an FP32 ru
 // with one atomic per list (one per row took 190 us at 128^2 rows).
 __global__ void __launch_bounds__(1024) k_near_list(int n, int nx, int cutoff, int periodic,
                                                     int64_t light_pairs, int64_t heavy_pairs,
+                                                    int most_around,
                                                     const int *__restrict__ start,
                                                     int *__restrict__ tiles,
                                                     int *__restrict__ pieces, int last_piece,
@@ -66,7 +67,8 @@ __global__ void __launch_bounds__(1024) k_near_list(int n, int nx, int cutoff, i
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) around += __shfl_xor(around, off, 64);
-    const bool dense = near_pairs_reach(np, around, nx, cutoff, light_pairs);
+    const bool dense = around >= most_around ||
+                       near_pairs_reach(np, around, nx, cutoff, light_pairs);
     const bool heavy = near_pairs_reach(np, around, nx, cutoff, heavy_pairs);
     const int nt = dense ? 0 : (np + kNearTile - 1) / kNearTile;
     int J[2], inc;
@@ -489,6 +491,10 @@ static void near_launch(const NearArgs &a, int logn, hipStream_t s) {
     const int64_t cells = bin_min64(a.n, a.cells), pieces_most = cells + a.n / kNearTargets;
     const int64_t heavy = pieces_most <= kNearFewPieces ? 0 : kNearHeavy;
     const int64_t light = heavy == 0 || cells <= kNearFewCells ? 0 : kNearLight;
+    // a tile's wave takes the rows around one after the other: rows with far more
+    // particles around them than the mean, or very many, go by cells too
+    const int64_t w = 2 * a.cutoff + 1, mean4 = 4 * w * w * a.n / (a.cells / a.nx);
+    const int most_around = (int)bin_min64(kNearMostAround, bin_max64(kNearMostAround / 4, mean4));
     // blocks loop over the pieces, which may be fewer (with none at all, 32600
     // blocks of 256 threads take 8.7 us, 3200 2.5)
     const int64_t most_rows = heavy > 0 ? near_rows_most(a.n, a.nx, a.cutoff, heavy) : rows;
@@ -496,14 +502,14 @@ static void near_launch(const NearArgs &a, int logn, hipStream_t s) {
     const unsigned blocks256 = (unsigned)bin_min64(wide, 32768);
     const unsigned blocks64 = (unsigned)bin_min64(pieces_most, 32768);
     hipLaunchKernelGGL(k_near_list, dim3((rows + 15) / 16), dim3(1024), 0, s, a.ncell, a.nx,
-                       a.cutoff, a.periodic, light, heavy, a.start, tiles, pieces, (int)most - 1, counts);
+                       a.cutoff, a.periodic, light, heavy, most_around, a.start, tiles, pieces, (int)most - 1, counts);
     // launched where the particles suffice for one row of the kind
     if (near_pairs_reach(a.n, a.n, a.nx, a.cutoff, heavy))
         hipLaunchKernelGGL((k_near_cells<T, POW2, kNearThreads>), dim3(blocks256), dim3(kNearThreads),
                            0, s, a.ncell, logn, a.cutoff, a.periodic, a.start, a.scell, sorted,
                            pieces + most - 1, -1, counts + 2, T(a.inv_h), (out4<T> *)a.staged,
                            a.accumulate);
-    if (heavy > 0 && near_pairs_reach(a.n, a.n, a.nx, a.cutoff, light))
+    if (heavy > 0 && (a.n >= most_around || near_pairs_reach(a.n, a.n, a.nx, a.cutoff, light)))
         hipLaunchKernelGGL((k_near_cells<T, POW2, 64>), dim3(blocks64), dim3(64), 0, s, a.ncell, logn,
                            a.cutoff, a.periodic, a.start, a.scell, sorted, pieces, 1, counts + 1,
                            T(a.inv_h), (out4<T> *)a.staged, a.accumulate);
