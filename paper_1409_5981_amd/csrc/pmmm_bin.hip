@@ -875,12 +875,31 @@ __global__ void __launch_bounds__(1024) k_bin_small(
     int key = 0, slot = 0;
     if (act) key = cell_record(x, y, z, q, i, inv_h, nc, topz, periodic, rec);
     for (int d = tid; d < 2 * nb; d += 1024) cur[d] = 0;
+    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     __syncthreads();
     constexpr int U = 8;
     for (int base = tid; base < np; base += 1024 * U) {
         int kv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) kv[u] = keys[base + u * 1024 < np ? base + u * 1024 : 0];
+        // Where the wave's first 64 keys agree, one lane counts for all that hold
+        // the same cell (a wave's keys are all before t0 or all from it on): 64
+        // additions to one address are serial, and a binning of 31270 particles
+        // in one cell took 38 us, now 20.  Tried for every key: 2 us of the 42
+        // of 32768 uniform particles on 16^3 cells.
+        if (__all(kv[0] == __builtin_amdgcn_readfirstlane(kv[0]))) {
+            for (int u = 0; u < U; ++u) {
+                const int j = base + u * 1024;
+                if (j < np) {
+                    int *c = j < t0 ? cur : rest;
+                    const int k0 = __builtin_amdgcn_readfirstlane(kv[u]);
+                    const uint64_t same = __ballot(kv[u] == k0);
+                    if (kv[u] != k0) atomicAdd(&c[kv[u]], 1);
+                    else if ((same & lt) == 0) atomicAdd(&c[k0], __popcll(same));
+                }
+            }
+            continue;
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = base + u * 1024;
@@ -925,7 +944,6 @@ __global__ void __launch_bounds__(1024) k_bin_small(
     if (blockIdx.x == 0 && tid == 0) start[K] = (int)np;
     // place the tile
     const uint64_t peers = digit_peers(act, key, bits);
-    const uint64_t lt = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     const int rank = __popcll(peers & lt);
     for (int w = 0; w < kSmallTile / 64; ++w) {
         __syncthreads();

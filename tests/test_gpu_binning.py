@@ -107,3 +107,39 @@ def test_binning_buckets_of_many_chunks(n, n_cells, p, share, prec):
     assert_parity(res, ref.phi, ref.grad, prec, f"large bucket {n} on {n_cells}^3 {prec}")
     again, _ = gpu_far(ps, precision=prec, plan=plan)
     assert all(np.array_equal(res[x], again[x]) for x in res)
+
+
+@pytest.mark.parametrize("n,run,prec", [(20000, 12100, "f32"), (9000, 8990, "f64")])
+def test_small_binning_with_a_run_of_one_cell(n, run, prec):
+    """The two-launch binning counts runs of one cell by whole waves: a run that
+    ends inside a wave, then other cells."""
+    dt = np.float32 if prec == "f32" else np.float64
+    rng = np.random.default_rng(n)
+    pos = rng.random((n, 3)) * 16
+    pos[:run] = np.array([5, 9, 3]) + rng.random((run, 3))
+    pos = (pos / 16).astype(dt)
+    q = (rng.random(n) / n).astype(dt)
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, 16, 3, "periodic")
+    res, plan = gpu_far(ps, precision=prec)
+    ref = opm.far_field(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps))
+    assert_parity(res, ref.phi, ref.grad, prec, f"run of {run} in {n} {prec}")
+
+
+@pytest.mark.parametrize("n,prec", [(20000, "f32"), (30000, "f32"), (30000, "f64")])
+def test_p2m_of_a_three_cell_box(n, prec):
+    """A box of 3 x 1 x 1 cells at c = 1: crowded cells reduced whole by a
+    block, and above 8192 particles a cell as items."""
+    dt = np.float32 if prec == "f32" else np.float64
+    rng = np.random.default_rng(n)
+    pos = (rng.random((n, 3)) * np.array([3, 1, 1]) / 32).astype(dt)
+    top = (np.array([3, 1, 1]) / 32).astype(dt)
+    pos = np.where(pos >= top, np.nextafter(top, dt(0)), pos)
+    q = (rng.random(n) / n).astype(dt)
+    ps = inputs.ParticleSet(pos[:, 0].copy(), pos[:, 1].copy(), pos[:, 2].copy(), q, 3, 5, "open",
+                            box=3 / 32, shape=(3, 1, 1))
+    res, _ = gpu_far(ps, precision=prec, cutoff=1)
+    ref = opm.far_field(ps.pos, ps.q.astype(np.float64), oracle_cfg(ps, 1))
+    # the middle cell's far field is zero: rounding of the convolution only
+    end = (np.floor(ps.x.astype(np.float64) * 32) != 1)
+    assert_parity({k: v[end] for k, v in res.items()}, ref.phi[end], ref.grad[end], prec,
+                  f"three cells {n} {prec}")
