@@ -39,10 +39,12 @@ int hip_fail(hipError_t e, const char *what) {
 // particles, one wave each.
 static int dense_threshold_for(int group) { return 16 * group; }
 
-// Up to this many particles a dense cell is one work item, reduced by one block
-// (64 x 512 particles for its four waves at worst), so that no launch adds
-// partial sums: 2 us of a call of 40.
+// Up to this many particles, and kWholeCellMean per cell of the box, a dense
+// cell is one work item, reduced by one block, so that no launch adds partial
+// sums: 2 us of a call of 40.  In a box of one cell the block's turns of 2048
+// particles take longer than that: 26880 particles, p = 5, P2M 43 us against 13 as items.
 constexpr int64_t kWholeCellMaxN = int64_t(1) << 15;
+constexpr int64_t kWholeCellMean = 8192;
 
 // From this many particles on, L2P writes its results in sorted order and a
 // second kernel sends them back to the caller's order (fewer, wider random
@@ -411,8 +413,14 @@ static int group_for(double mean) {
     return 64;
 }
 
-// What one call computes: the far field (pmmm_far_*), the near field alone
-// (pmmm_near_*) or both with one binning (pmmm_total_*).
+// Cells of the caller's box.
+static int64_t box_cells(const Plan *pl) {
+    return pl->open ? (int64_t)pl->lim[0] * pl->lim[1] * pl->lim[2] : pl->K;
+}
+static int whole_cells(const Plan *pl, int64_t n) {
+    return n <= kWholeCellMaxN && n <= kWholeCellMean * box_cells(pl);
+}
+
 // Sizes and tables of a plan's convolution stages.  An open box's planes
 // [lim z, n) hold no moments and no target, so the stages stop at its top.
 static FFTArgs plan_conv(const Plan *pl) {
@@ -431,6 +439,8 @@ static FFTArgs plan_conv(const Plan *pl) {
     return f;
 }
 
+// What one call computes: the far field (pmmm_far_*), the near field alone
+// (pmmm_near_*) or both with one binning (pmmm_total_*);
 // kHierFine / kHierTotal: the fine level of a hierarchy (and its near field),
 // added into outputs that already hold the coarse far field
 enum CallMode { kFar = 0, kNear = 1, kTotal = 2, kHierFine = 3, kHierTotal = 4 };
@@ -541,7 +551,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
     const bool sorted_stage = mode == kNear || mode == kTotal || mode == kHierTotal;
     const int group = pl->tune_group > 0 ? pl->tune_group : group_for((double)n / (double)pl->K);
     const int dense_thr = dense_threshold_for(group);
-    const int whole = n <= kWholeCellMaxN;
+    const int whole = whole_cells(pl, n);
 
     {
         StageTimer t(pl, PMMM_STAGE_BIN, s, timed);
@@ -665,7 +675,7 @@ static int enqueue_impl(pmmm_plan_s *pl, CallMode mode, int64_t n, const T *x, c
         a.sorted = pb.sorted;
         a.inv_h = pl->inv_h;
         a.nx = pl->open ? pl->lim[0] : pl->n;
-        a.cells = pl->open ? (int64_t)pl->lim[0] * pl->lim[1] * pl->lim[2] : pl->K;
+        a.cells = box_cells(pl);
         a.lists = pb.lists;
         a.pieces = pb.slot;   // free after the binning
         a.small = pl->small;
@@ -1142,7 +1152,7 @@ static int class_enqueue(pmmm_batch_s *b, BatchClass &c, const float *x, const f
         const int ns = (int)c.members.size();
         const int group = group_for((double)c.tot_np / ((double)pl->K * ns));
         const int dense_thr = dense_threshold_for(group);
-        const int whole = c.max_np <= kWholeCellMaxN;
+        const int whole = whole_cells(pl, c.max_np);
         BinArgs bn{};
         bn.n = 0;
         bn.x = x;

@@ -179,10 +179,18 @@ __global__ void __launch_bounds__(256) k_p2m(int K, int nlight, const int *__res
         for (int c = 0; c < NV; ++c) acc[c] += __shfl_xor(acc[c], off, 64);
     }
     if (write) {
+        // every lane of the group holds every sum; lane L stores the components
+        // L, L + G, ..., chosen by selects (a store per component under its own
+        // lane mask compiled to thousands of mask operations: 550 particles per
+        // cell on 4^3 cells, p = 6 51 us, now 15)
         const int at = moment_place(cell, order);
 #pragma unroll
-        for (int c = 0; c < NV; ++c)
-            if ((c & (G - 1)) == lane) M[(int64_t)c * K + at] = acc[c];
+        for (int c0 = 0; c0 < NV; c0 += G) {
+            T v = acc[c0];
+#pragma unroll
+            for (int k = 1; k < G && c0 + k < NV; ++k) v = lane == k ? acc[c0 + k] : v;
+            if (c0 + lane < NV) M[(int64_t)(c0 + lane) * K + at] = v;
+        }
     }
 }
 
