@@ -890,7 +890,6 @@ static int multi_impl(pmmm_plan_s *pl, int64_t n, const float *x, const float *y
         a.ld = nsets;
         a.start = pl->start;
         a.perm = pl->perm;
-        a.zero_count = nullptr;
         a.sorted = pl->sorted;
         a.q = q + s0;
         a.M = pl->mM;

@@ -852,8 +852,6 @@ template <typename T>
 hipError_t launch_near(const NearArgs &a, hipStream_t s);
 // Ints of the near field's tile list for n particles on ncell^3 cells.
 int64_t near_list_ints(int64_t n, int ncell);
-// p[0 .. count) = 0 with a fill kernel.
-hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s);
 
 // Plan-time transfer kernel (FP64 on the GPU), stored in precision T.
 struct GreenArgs {
@@ -887,7 +885,6 @@ struct MultiArgs {
     int64_t np;                     // particles
     int64_t ld;                     // row stride of q and the outputs (sets)
     const int *start, *perm;
-    int *zero_count;                // counts to reset for the next binning (or null)
     const void *sorted;             // particle4<float>[np]
     const float *q;                 // [np][ld], this chunk's first set at column 0
     float *M;                       // [K][P+1][S] moments and q|u|^2; then L [K][P][S]

@@ -65,17 +65,12 @@ __global__ void __launch_bounds__(256) k_p2m_multi(int K, int cells_per_block,
                                                    const particle4<float> *__restrict__ sorted,
                                                    const int *__restrict__ perm,
                                                    const float *__restrict__ q, int64_t ld, int S,
-                                                   float *__restrict__ M,
-                                                   int *__restrict__ zero_count) {
+                                                   float *__restrict__ M) {
     constexpr int P = nreal(PO);
     constexpr int RS = stage_row(P + 1);     // harmonics, then |u|^2
     __shared__ __align__(16) float rb[4][64 * RS];
     __shared__ int oi[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (zero_count != nullptr) {
-        const int gid = blockIdx.x * 256 + threadIdx.x;
-        if (gid < K) zero_count[gid] = 0;
-    }
     float *R = rb[w];
     int *O = oi[w];
     const int c0 = blockIdx.x * cells_per_block;
@@ -772,7 +767,7 @@ static hipError_t multi_particles(const MultiArgs &a, int stage, hipStream_t s) 
     if (stage == 0) {
         hipLaunchKernelGGL((k_p2m_multi<PO>), dim3(grid), dim3(256), 0, s, K,
                            kMultiCellsPerBlock, a.start, (const particle4<float> *)a.sorted,
-                           a.perm, a.q, a.ld, a.nsets, a.M, a.zero_count);
+                           a.perm, a.q, a.ld, a.nsets, a.M);
     } else {
         if (a.np == 0) return hipSuccess;
         hipLaunchKernelGGL((k_l2p_multi<PO>), dim3(grid), dim3(256), 0, s, K,

@@ -532,18 +532,6 @@ hipError_t launch_near(const NearArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) k_zero_ints(int *__restrict__ p, int64_t count) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0;
-}
-
-hipError_t launch_zero_ints(int *p, int64_t count, hipStream_t s) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_ints, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, p,
-                       count);
-    return hipGetLastError();
-}
-
 int64_t near_list_ints(int64_t n, int ncell) { return max_row_tiles(n, ncell); }
 
 template hipError_t launch_near<float>(const NearArgs &, hipStream_t);

@@ -226,3 +226,23 @@ def test_near_crowded_cell_in_an_open_box(shape, cutoff, n, prec, dt):
     assert_parity(res, nphi, ng, prec, f"crowded {shape} c={cutoff} {prec}")
     again, _ = _gpu(ps, prec, "near", plan=plan)
     assert all(np.array_equal(res[k], again[k]) for k in res)
+
+
+@pytest.mark.parametrize("prec,dt", [("f32", np.float32), ("f64", np.float64)])
+@pytest.mark.parametrize("n,n_cells", [(40, 4), (4000, 4), (6000, 32)])
+def test_near_beside_coincident_particles(prec, dt, n, n_cells):
+    """Two particles at one position leave every value of all others finite and
+    as with one particle of both charges there, by cells (few particles and
+    crowded cells) and in tiles (the sparse 32^3 mesh)."""
+    ps = _set(n, n_cells, 3, "open", 65, dt, neutral=False)
+    ps.x[7], ps.y[7], ps.z[7] = ps.x[30], ps.y[30], ps.z[30]
+    res, _ = _gpu(ps, prec, "near", cutoff=1)
+    others = np.ones(n, bool)
+    others[[7, 30]] = False
+    assert np.isinf(res["phi"][~others]).all()
+    assert np.isfinite(res["phi"][others]).all() and np.isfinite(res["grad"][others]).all()
+    pair, pairg = exact.near(np.concatenate([ps.pos[others], ps.pos[30:31]]),
+                             np.concatenate([ps.q[others], [float(ps.q[7]) + float(ps.q[30])]]).astype(np.float64),
+                             oracle_cfg(ps, 1))
+    assert_parity({k: v[others] for k, v in res.items()}, pair[:-1], pairg[:-1], prec,
+                  f"beside coincident n={n} {prec}")
