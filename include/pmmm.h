@@ -249,8 +249,13 @@ int pmmm_total_f64(pmmm_plan plan, int64_t n, const double *x, const double *y,
  * pmmm_hier_far_f32 returns the first two parts, pmmm_hier_total_f32 all
  * three; arguments, layouts, ownership and stream semantics as
  * pmmm_far_f32 (the outputs are overwritten).  The fine level costs
- * O(((2c+1) r)^3 (p+1)^4) per fine cell.  pmmm_hier_sync_status reports a
- * particle outside the box as PMMM_EDOMAIN.  Errors: PMMM_EINVAL for a bad
+ * O(((2c+1) r)^3 (p+1)^4) per fine cell.  Beside its two plans a hierarchy
+ * holds the kernel values at the fine displacements, (2D+1)^3 (2p+1)^2 floats
+ * with D = (c+1) r - 1, and for most meshes of 4^3 coarse cells and more their
+ * matrices in the matrix cores' order, about (2D+1)^3 (p+1)^4 floats and at
+ * most 512 MiB; where those cannot be allocated the hierarchy is made without
+ * them.  pmmm_hier_sync_status reports a particle outside the box as
+ * PMMM_EDOMAIN.  Errors: PMMM_EINVAL for a bad
  * argument or refine, PMMM_EUNSUPPORTED for a mesh the hierarchy does not
  * take, plus those of pmmm_plan_create and pmmm_far_f32. */
 int pmmm_hier_create(const pmmm_params *coarse, int refine, void *stream, pmmm_hier *out);
