@@ -812,12 +812,12 @@ constexpr int64_t kNearHeavy = 49152;
 // 25 us; 2166 clustered on 10^3, c = 2 294 -> 49; 10637 clustered on 33 x 20 x 3,
 // c = 1 919 -> 227.
 constexpr int64_t kNearFewCells = 4096;
+constexpr int64_t kNearFewPieces = 1536;
 // A row with so many particles around it goes by cells (a quarter of it where
 // that is four times the mean): half of 10799 particles in one cell of 27 x 36 x
 // 16, c = 2 584 us with all rows in tiles, 701 with the rows beside the crowd in
 // tiles, 214 by this rule.
 constexpr int64_t kNearMostAround = 4096;
-constexpr int64_t kNearFewPieces = 1536;
 // np particles in the nx cells of a row's box, around in the rows around it (on
 // the host, all particles for both: can any row reach it?).  Any 32-bit counts:
 // from 2^30 on the answer is yes, and the product would not fit 64 bits.

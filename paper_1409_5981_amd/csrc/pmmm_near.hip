@@ -502,7 +502,8 @@ static void near_launch(const NearArgs &a, int logn, hipStream_t s) {
     const unsigned blocks256 = (unsigned)bin_min64(wide, 32768);
     const unsigned blocks64 = (unsigned)bin_min64(pieces_most, 32768);
     hipLaunchKernelGGL(k_near_list, dim3((rows + 15) / 16), dim3(1024), 0, s, a.ncell, a.nx,
-                       a.cutoff, a.periodic, light, heavy, most_around, a.start, tiles, pieces, (int)most - 1, counts);
+                       a.cutoff, a.periodic, light, heavy, most_around, a.start, tiles, pieces,
+                       (int)most - 1, counts);
     // launched where the particles suffice for one row of the kind
     if (near_pairs_reach(a.n, a.n, a.nx, a.cutoff, heavy))
         hipLaunchKernelGGL((k_near_cells<T, POW2, kNearThreads>), dim3(blocks256), dim3(kNearThreads),
